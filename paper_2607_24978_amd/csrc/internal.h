@@ -67,6 +67,27 @@ struct Tile {
     int nblocks() const { return nbz * nby * nbx; }
 };
 
+// Cache policy of a pass.  The memory-side cache (256 MB) holds what the last
+// pass wrote if that was written with ordinary stores and fits; a pass that
+// walks its tiles' x-planes in the opposite order then finds the end of the
+// state, and not its evicted beginning.  Odd passes of a call march down
+// (kPassReverse).  Whether the written state stays cached (ordinary stores)
+// or streams past (kPassNtStore) depends on the bytes a pass touches: up to
+// twice the cache the reuse wins, beyond it the streaming stores do.
+// Measured on MI355X, us per pass, ordinary / streaming: one field 256^3 FP32
+// (256 MiB touched) 41.5 / 59, two fields 128^3 FP64 (256 MiB) 29.8 / 39.7,
+// two fields 256^3 FP32 (512 MiB) 99.7 / 103.5 (106 ordinary without the
+// reversed passes), one field 384^3 FP64 (864 MiB) 359 / 346, two fields
+// 512^3 FP32 (2 GiB) 741 / 722.
+constexpr int kPassNtStore = 1;
+constexpr int kPassReverse = 2;
+constexpr size_t kMallBytes = size_t(256) << 20;
+// Reduced lattices stream as soon as the two states do not fit: 4096^2, two
+// fields, FP32 (512 MiB) 109 / 105.
+inline int pass_flags(size_t touched, int pass, int dim = 3) {
+    return (touched > (dim == 3 ? 2 : 1) * kMallBytes ? kPassNtStore : 0) | (pass & 1 ? kPassReverse : 0);
+}
+
 // One pass over the lattice: optional drift, kick, lattice sums and the
 // last-workgroup background update.
 //
@@ -82,7 +103,7 @@ struct PassArgs {
     int drift;      // 1: drift f by cd * p before the kick
     int write_out;  // 0: reduction only (no field writes, no kick)
     int rec;        // observable slot for this pass, -1: none
-    int flags;      // bit 0: nontemporal stores, bit 1: nontemporal loads
+    int flags;      // kPassNtStore | kPassReverse
     double kt;      // kick multiplier for the stored momenta
     double kb;      // kick multiplier for the synchronised momenta (energies)
     double h_next;  // drift step of the following pass, 0: call ends here
@@ -259,6 +280,7 @@ Tile default_tile(int N, cl_precision prec, int nf);
 // kernel's limits.  Returns false if not.
 bool finalize_tile(Tile& t, int N, cl_precision prec);
 // LDS of a pass for `arrays` stencil arrays (the fields, plus the tensor
+int march_length(int N, int tiles, int per_round);
 // components when gravitational waves are on).
 size_t pass_lds_bytes(const Tile& t, cl_precision prec, int arrays);
 // All valid tiles the autotuner tries for a lattice.

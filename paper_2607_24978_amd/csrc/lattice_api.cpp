@@ -128,7 +128,7 @@ PassArgs base_args(cl_lattice* h, int in) {
     PassArgs a{};
     a.in = h->buf[in];
     a.out = h->buf[in ^ 1];
-    a.flags = h->pass_flags;
+    a.flags = 0;
     a.N = h->N;
     a.TZ = h->tile.TZ;
     a.TY = h->tile.TY;
@@ -194,6 +194,9 @@ struct PassSeq {
     hipError_t launch(PassArgs a) {
         a.partials = part(p & 1);
         a.obs = w.obs;
+        // buffers a pass reads or writes: the two states, and a Runge-Kutta
+        // scheme's one (low storage) or two (classic) more
+        a.flags = cl::pass_flags((2 + static_cast<size_t>(a.rk)) * state_bytes(h), p, h->dim);
         if (p == 0) {
             a.has_prev = 0;
             a.sc_in = h->sc;
@@ -855,8 +858,6 @@ cl_status cl_create_dim(int dim, int N, double dx, int n_fields, cl_precision pr
         }
         hipMemsetAsync(h->buf[pp], 0, bytes, h->stream);
     }
-    const char* nt = std::getenv("CL_PASS_FLAGS");
-    if (nt && nt[0]) h->pass_flags = std::atoi(nt);
     if (hipMalloc(&h->sc, sizeof(Scal)) != hipSuccess) return bail(CL_ENOMEM, "scalar block");
     if (hipMalloc(&h->scb, 2 * sizeof(Scal)) != hipSuccess) return bail(CL_ENOMEM, "scalar blocks");
     if (dim == 3) {
@@ -1622,6 +1623,13 @@ bool ensemble_tile(int N, cl_precision prec, cl::EnsMember& t, int item_sites, b
     t.nbz = N / t.TZ;
     t.nby = N / t.TY;
     t.nbx = N / t.CX;
+// Bytes a pass over all members touches: both state buffers of every one.
+size_t ens_bytes(const cl_ensemble* e) {
+    size_t b = 0;
+    for (const cl_lattice* h : e->m) b += 2 * state_bytes(h);
+    return b;
+}
+
     t.nitems = t.nbz * t.nby * t.nbx;
     // halo items must fit one per thread
     return 2 * BZ + 2 * t.TY <= 256;
@@ -1828,7 +1836,8 @@ cl_status cl_ensemble_step(cl_ensemble* e, cl_integrator integ, int n, cl_observ
         a.nitems = e->nitems;
         a.nmembers = nm;
         a.write_out = 1;
-        a.flags = 1;
+        const size_t touched = ens_bytes(e);
+        a.flags = cl::pass_flags(touched, 0);
         a.counter = e->d_counter;
         a.obs = e->d_obs;
         a.lds_bytes = static_cast<int>(e->lds);
@@ -1877,6 +1886,7 @@ cl_status cl_ensemble_step(cl_ensemble* e, cl_integrator integ, int n, cl_observ
                                          hipGetErrorString(err != hipSuccess ? err : e2));
         }
         err = hipGraphInstantiate(&e->gexec, g, nullptr, nullptr, 0);
+            d.flags = cl::pass_flags(touched, s + 1);
         hipGraphDestroy(g);
         if (err != hipSuccess) {
             e->gexec = nullptr;
@@ -1960,7 +1970,6 @@ cl_status cl_ensemble_autotune(cl_ensemble* e, int reps, char* report, size_t ca
             a.nmembers = nm;
             a.drift = 0;
             a.write_out = 1;
-            a.flags = 1;
             a.rec = -1;
             a.prev_rec = -1;  // no records: the scalar steps of these passes are not kept
             a.counter = e->d_counter;
@@ -1992,6 +2001,7 @@ cl_status cl_ensemble_autotune(cl_ensemble* e, int reps, char* report, size_t ca
             std::snprintf(item, sizeof item, "%s{\"item_sites\":%d,\"two_rows\":%s,\"us\":%.2f}", first ? "" : ",",
                           sites, rows ? "true" : "false", ms * 1e3);
             js += item;
+                    a.flags = cl::pass_flags(ens_bytes(e), q);
             first = false;
             if (best_ms < 0.0f || ms < best_ms) {
                 best_ms = ms;

@@ -15,7 +15,7 @@
 // since the drift of halo cells needs the old momenta of neighbouring tiles.
 //
 // Blocking: a workgroup owns a TZ x TY tile of (z, y) and marches over CX
-// x-planes.  Each x-plane of drifted f (tile plus a one-cell y/z halo) is
+// x-planes, up or (kPassReverse) down.  Each x-plane of drifted f (tile plus a one-cell y/z halo) is
 // staged in LDS (double-buffered, one barrier per plane); the x-neighbours
 // live in registers.  Each thread owns V consecutive z values (16-byte
 // vector loads and stores) in RY rows.
@@ -51,16 +51,8 @@ template <typename T> struct NatVec;
 template <> struct NatVec<float> { typedef float type __attribute__((ext_vector_type(4))); };
 template <> struct NatVec<double> { typedef double type __attribute__((ext_vector_type(2))); };
 
-// Streaming variants: the nontemporal hint keeps data that is not reused in
-// this pass from displacing the halo lines in the caches.
-template <typename T>
-__device__ __forceinline__ void vload_nt(const T* p, T (&out)[VecOf<T>::V]) {
-    using NV = typename NatVec<T>::type;
-    NV v = __builtin_nontemporal_load(reinterpret_cast<const NV*>(p));
-#pragma unroll
-    for (int i = 0; i < VecOf<T>::V; ++i) out[i] = v[i];
-}
-
+// Streaming store: the nontemporal hint keeps the written state, which this
+// pass does not read again, from displacing the halo lines in the caches.
 template <typename T>
 __device__ __forceinline__ void vstore_nt(T* p, const T (&in)[VecOf<T>::V]) {
     using NV = typename NatVec<T>::type;
@@ -434,8 +426,10 @@ __device__ __forceinline__ void march_tile(const TileJob& J, unsigned char* smem
         fout[j] = static_cast<T*>(J.out) + j * N;
         pout[j] = static_cast<T*>(J.out) + (NA + j) * N;
     }
-    const bool nt_store = J.flags & 1;
-    const bool nt_load = J.flags & 2;
+    const bool nt_store = J.flags & kPassNtStore;
+    const bool rev = J.flags & kPassReverse;
+    // x of the k-th plane of the march
+    auto xof = [&](int k) { return rev ? x0 + CX - 1 - k : x0 + k; };
     T* auxf[NF];
     T* auxp[NF];
 #pragma unroll
@@ -528,20 +522,15 @@ __device__ __forceinline__ void march_tile(const TileJob& J, unsigned char* smem
 #pragma unroll
         for (int j = 0; j < NA; ++j) {
             if (own) {
-                const size_t obase = static_cast<size_t>((x0 + ko + N) % N) * plane;
+                const size_t obase = static_cast<size_t>((xof(ko) + N) % N) * plane;
 #pragma unroll
                 for (int r = 0; r < RY; ++r) {
-                    if (nt_load) {
-                        vload_nt(fin[j] + obase + yrow[r], rf[S_][j][r]);
-                        vload_nt(pin[j] + obase + yrow[r], rp[S_][j][r]);
-                    } else {
-                        vload(fin[j] + obase + yrow[r], rf[S_][j][r]);
-                        vload(pin[j] + obase + yrow[r], rp[S_][j][r]);
-                    }
+                    vload(fin[j] + obase + yrow[r], rf[S_][j][r]);
+                    vload(pin[j] + obase + yrow[r], rp[S_][j][r]);
                 }
             }
             if (halo) {
-                const size_t hbase = static_cast<size_t>((x0 + kh + N) % N) * plane;
+                const size_t hbase = static_cast<size_t>((xof(kh) + N) % N) * plane;
 #pragma unroll
                 for (int q = 0; q < HI; ++q) {
                     if (h_goff[q] < 0) continue;
@@ -645,7 +634,7 @@ __device__ __forceinline__ void march_tile(const TileJob& J, unsigned char* smem
     T y0c[RK == 2 ? 2 : 1][NF][RY][V], y0n[RK == 2 ? 2 : 1][NF][RY][V];
     auto aux_load = [&](int k, T (&dst)[RK ? 2 : 1][NF][RY][V], T (&ydst)[RK == 2 ? 2 : 1][NF][RY][V]) {
         if constexpr (RK) {
-            const size_t base = static_cast<size_t>(x0 + k) * static_cast<size_t>(N) * rs;
+            const size_t base = static_cast<size_t>(xof(k)) * static_cast<size_t>(N) * rs;
 #pragma unroll
             for (int j = 0; j < NF; ++j)
 #pragma unroll
@@ -684,7 +673,7 @@ __device__ __forceinline__ void march_tile(const TileJob& J, unsigned char* smem
     // halo loads of plane x+1+HPD into the same halo set, then plane x is
     // computed.
     auto body = [&](auto Sc, auto Hc, int i) {
-        const int x = x0 + i;
+        const int x = xof(i);
         const int buf = i & 1;
         consume(Sc, Hc, nxt, pn, i + 1 < CX ? (buf ^ 1) : -1);
         if constexpr (HPD == PD) {
@@ -735,8 +724,8 @@ __device__ __forceinline__ void march_tile(const TileJob& J, unsigned char* smem
                     const T f = fs[j];
                     const T zm = v == 0 ? zm0[j] : cur[j][k][v - 1];
                     const T zp = v == V - 1 ? zp0[j] : cur[j][k][v + 1];
-                    const T xp = nxt[j][k][v];
-                    const T nb = ((prev[j][k][v] + xp) + (ym[j][v] + yp[j][v])) + (zm + zp);
+                    const T xp = rev ? prev[j][k][v] : nxt[j][k][v];
+                    const T nb = ((prev[j][k][v] + nxt[j][k][v]) + (ym[j][v] + yp[j][v])) + (zm + zp);
                     const T F = fmad(kL, fmad(T(-6), f, nb), -(kV * dV[j]));
                     const T po = pc[j][k][v];
                     const T gx = xp - f, gy = yp[j][v] - f, gz = zp - f;
@@ -783,7 +772,8 @@ __device__ __forceinline__ void march_tile(const TileJob& J, unsigned char* smem
                         const T f = cur[j][k][v];
                         const T zm = v == 0 ? zm0[j] : cur[j][k][v - 1];
                         const T zp = v == V - 1 ? zp0[j] : cur[j][k][v + 1];
-                        const T ax = nxt[j][k][v] - f, bx = f - prev[j][k][v];
+                        const T xn = rev ? prev[j][k][v] : nxt[j][k][v], xb = rev ? nxt[j][k][v] : prev[j][k][v];
+                        const T ax = xn - f, bx = f - xb;
                         const T ay = yp[j][v] - f, by = f - ym[j][v];
                         const T az = zp - f, bz = f - zm;
                         sxx = fmad(ax, ax, fmad(bx, bx, sxx));
@@ -1140,7 +1130,8 @@ __global__ __launch_bounds__(256, (NF == 1 && MAXRY == 1) ? 3 : 1) void ensemble
         __syncthreads();
         const int it = item_s;
         if (it >= E.nitems) break;
-        const EnsItem I = E.items[it];
+        // (odd passes also take the items in the opposite order)
+        const EnsItem I = E.items[E.flags & kPassReverse ? E.nitems - 1 - it : it];
         const EnsMember& M = E.members[I.member];
         const double kt = E.ckt * M.dt, kb = E.ckb * M.dt;
         TileJob J;
