@@ -1078,21 +1078,49 @@ bool finalize_tile(Tile& t, int N, cl_precision prec) {
 
 Tile default_tile(int N, cl_precision prec, int nf) {
     const int V = prec == CL_FP32 ? 4 : 2;
+// x-planes a workgroup marches over: the divisor of N with the cheapest
+// schedule, counted in plane times -- rounds of workgroups over the CUs
+// (`per_round` run at a time), each paying its planes and about eight more
+// for its start (loads in flight, the scalar step) and its end (the sums).
+int march_length(int N, int tiles, int per_round) {
+    int best = N;
+    long best_cost = -1;
+    for (int cx = N; cx >= 1; --cx) {
+        if (N % cx) continue;
+        const long blocks = static_cast<long>(tiles) * (N / cx);
+        if (blocks > kTunedPassBlocks && best_cost >= 0) break;
+        if (blocks > kMaxPassBlocks) break;
+        const long cost = (blocks + per_round - 1) / per_round * (cx + 8);
+        if (best_cost < 0 || cost < best_cost) {
+            best = cx;
+            best_cost = cost;
+        }
+    }
+    return best;
+}
+
+// Tile of a lattice that is not tuned: full rows up to 64 threads along z,
+// and as many rows as make up the workgroup.  Its size follows the lattice:
+// one wave (whose barriers cost nothing) while 64-thread tiles one plane
+// long number at most two per CU, two waves up to 64^3, four while the state
+// reuses the memory-side cache, and eight beyond it, where the halo rows of
+// short tiles are read from HBM again.  Measured, us per pass against the
+// former tile (256 threads, marches of at least four planes): one field 32^3
+// FP64 8.9 / 11.1, two fields 64^3 FP32 14.9 / 18.0, two fields 128^3 FP32
+// 24.2 / 30.9, two fields 256^3 FP32 99.7 / 108.9, one field 384^3 FP64
+// 344 / 382, two fields 512^3 FP32 721 / 798 (with the cache policy above).
     Tile t;
     t.TZ = N < 64 * V ? N : 64 * V;
+    const size_t sites = static_cast<size_t>(N) * N * N;
+    const size_t touched = 4 * nf * sites * (prec == CL_FP32 ? 4 : 8);
+    const int threads = sites / V <= 32768 ? 64 : sites / V <= 131072 ? 128 : touched <= 2 * kMallBytes ? 256 : 512;
     const int BZ = t.TZ / V;
     t.RY = 1;
-    int RL = 256 / BZ;
-    while (RL > 1 && (RL > N || N % RL)) RL >>= 1;
-    t.TY = RL * t.RY;
-    if ((N / t.TZ) * (N / t.TY) > kTunedPassBlocks && N % (2 * RL) == 0) {
-        t.RY = 2;  // two rows per thread: half the workgroups
-        t.TY = 2 * RL;
-    }
-    const int tiles = (N / t.TZ) * (N / t.TY);
-    t.CX = N;
-    while (t.CX > 4 && tiles * (N / t.CX) < 512 && (t.CX % 2 == 0)) t.CX /= 2;
-    (void)nf;
+    int TY = threads / BZ;
+    while (TY > 1 && (TY > N || N % TY)) TY >>= 1;
+    t.TY = TY;
+    t.CX = march_length(N, (N / t.TZ) * (N / t.TY), 256);
+    t.PD = t.CX >= 32 ? 2 : 1;
     finalize_tile(t, N, prec);
     return t;
 }
@@ -1105,8 +1133,13 @@ Tile default_tile(int N, cl_precision prec, int nf) {
 // release per item), then marches its tile and leaves its sums.  The last
 // workgroup to leave resets the counters for the next pass.  MAXRY: the
 // largest rows per thread among the members; with one row everywhere the
-// kernel has only that path, with its halo ring at depth 2, and fits two
-// waves per SIMD.
+// kernel has only that path, with its halo ring at depth 2 and three (one
+// field) or one wave per SIMD.  With two rows one field is held to two waves
+// per SIMD, which takes a prefetch depth of 2: a plane step is bound by its
+// barrier and LDS round trips, so a second workgroup per CU is worth more
+// than deeper prefetch (two fields would spill, and keep one wave).  48 x 32^3 + 32 x 64^3 + 16 x 128^3, one
+// field, FP32 (696 MB per pass): 157 us = 4.4 TB/s against 200 at depth 4 and
+// one wave per SIMD (164 with one row and three waves).
 // Scalar blocks of an ensemble member inside a call: pass p starts from the
 // scalars pass p - 1 used (the member's own block for p = 1 and p = 0) and
 // leaves its own in scratch block p mod 2.
@@ -1288,7 +1321,7 @@ void candidate_tiles(int N, cl_precision prec, int nf, Tile* out, int* count, in
                     if (TY > N) continue;
                     for (int CX = 2; CX <= N; CX *= 2)
                         for (int PD : {1, 2, 4}) {
-                            if (CX != N && (CX < 4 || CX > 256)) continue;
+                            if (CX != N && (CX < (N > 64 ? 4 : 2) || CX > 256)) continue;
                             Tile t;
                             t.TZ = TZ;
                             t.TY = TY;
