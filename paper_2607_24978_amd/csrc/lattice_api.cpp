@@ -1597,10 +1597,6 @@ cl_status efail(cl_status st, const std::string& msg) {
         if (e_ != hipSuccess) return efail(CL_EDEVICE, std::string(#call) + ": " + hipGetErrorString(e_)); \
     } while (0)
 
-// Default layout: about 32k sites per work item, two rows per thread where
-// the lattice is tall enough.
-constexpr int kEnsItemSites = 32768;
-
 // Tile of one member: 256 threads, full rows when N <= 64 vectors, about
 // item_sites sites per work item.
 bool ensemble_tile(int N, cl_precision prec, cl::EnsMember& t, int item_sites, bool two_rows) {
@@ -1622,16 +1618,16 @@ bool ensemble_tile(int N, cl_precision prec, cl::EnsMember& t, int item_sites, b
     t.nbz = N / t.TZ;
     t.nby = N / t.TY;
     t.nbx = N / t.CX;
+    t.nitems = t.nbz * t.nby * t.nbx;
+    // halo items must fit one per thread
+    return 2 * BZ + 2 * t.TY <= 256;
+}
+
 // Bytes a pass over all members touches: both state buffers of every one.
 size_t ens_bytes(const cl_ensemble* e) {
     size_t b = 0;
     for (const cl_lattice* h : e->m) b += 2 * state_bytes(h);
     return b;
-}
-
-    t.nitems = t.nbz * t.nby * t.nbx;
-    // halo items must fit one per thread
-    return 2 * BZ + 2 * t.TY <= 256;
 }
 
 // Work decomposition of all members for one (item size, rows per thread)
@@ -1721,6 +1717,31 @@ cl_status ens_upload_table(cl_ensemble* e, bool with_dt) {
     return CL_OK;
 }
 
+// Work-item size of an ensemble that is not tuned, two rows per thread where
+// the lattice is tall enough: about 32k sites, or fewer until at least every
+// second workgroup that can run at once has an item.  Measured (one field,
+// FP32, 512 workgroups at once), us per pass with 8k / 16k / 32k / 64k-site
+// items: 48 x 32^3 (192 .. 24 items) 22.7 / 27.1 / 40.4 / -, 32 x 64^3 (1024 ..
+// 128) 44.0 / 37.9 / 37.3 / 54.8, 16 x 128^3 (4096 .. 512) 134 / 117 / 108 / 109.
+int ens_item_sites(const cl_ensemble* e) {
+    int sites = 32768;
+    for (; sites > 8192; sites /= 2) {
+        long items = 0;
+        int maxTY = 0, maxTZ = 0, maxry = 1;
+        for (const cl_lattice* h : e->m) {
+            cl::EnsMember t{};
+            if (!ensemble_tile(h->N, e->prec, t, sites, true)) continue;
+            items += t.nitems;
+            maxTY = std::max(maxTY, t.TY);
+            maxTZ = std::max(maxTZ, t.TZ);
+            maxry = std::max(maxry, t.RY);
+        }
+        const size_t lds = cl::ensemble_lds_bytes(e->prec, e->nf, maxTY, maxTZ);
+        if (2 * items >= cl::ensemble_grid(e->prec, e->nf, lds, maxry)) break;
+    }
+    return sites;
+}
+
 void ens_free(cl_ensemble* e) {
     if (e->stream) hipStreamSynchronize(e->stream);
     if (e->gexec) hipGraphExecDestroy(e->gexec);
@@ -1771,7 +1792,7 @@ cl_status cl_ensemble_create(int n, cl_lattice* const* members, cl_ensemble** ou
         hipMemsetAsync(e->d_counter, 0, 64, e->stream) != hipSuccess ||
         hipStreamSynchronize(e->stream) != hipSuccess)
         return bail(CL_EDEVICE, "ensemble table upload");
-    const cl_status st = ens_layout(e, kEnsItemSites, true);
+    const cl_status st = ens_layout(e, ens_item_sites(e), true);
     if (st) {
         const std::string msg = g_err;
         return bail(st, msg);

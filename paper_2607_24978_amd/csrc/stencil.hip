@@ -1148,7 +1148,7 @@ __device__ __forceinline__ const Scal* ens_scal_before(const EnsMember& M, int p
 }
 
 template <typename T, int NF, int MAXRY>
-__global__ __launch_bounds__(256, (NF == 1 && MAXRY == 1) ? 3 : 1) void ensemble_pass(EnsArgs E) {
+__global__ __launch_bounds__(256, NF == 2 ? 1 : MAXRY == 2 ? 2 : 3) void ensemble_pass(EnsArgs E) {
     constexpr int NS = kSumsPerField * NF + 1;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     __shared__ double tot[kMaxSums];
@@ -1212,8 +1212,9 @@ __global__ __launch_bounds__(256, (NF == 1 && MAXRY == 1) ? 3 : 1) void ensemble
 #pragma unroll
         for (int k = 0; k < NS; ++k) acc[k] = 0.0;
         if constexpr (MAXRY == 2) {
-            if (M.RY == 2) march_tile<T, NF, 2, 1, 4, 0, 4, 0>(J, smem_raw, acc, prelude);
-            else march_tile<T, NF, 1, 1, 4, 0, 4, 0>(J, smem_raw, acc, prelude);
+            constexpr int PD = 2;
+            if (M.RY == 2) march_tile<T, NF, 2, 1, PD, 0, PD, 0>(J, smem_raw, acc, prelude);
+            else march_tile<T, NF, 1, 1, PD, 0, PD, 0>(J, smem_raw, acc, prelude);
         } else {
             march_tile<T, NF, 1, 1, 4, 0, 2, 0>(J, smem_raw, acc, prelude);
         }
