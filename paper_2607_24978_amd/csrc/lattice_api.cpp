@@ -1886,6 +1886,7 @@ cl_status cl_ensemble_step(cl_ensemble* e, cl_integrator integ, int n, cl_observ
             cl::EnsArgs d = a;
             follow(d, a);
             d.parity = s + 1;
+            d.flags = cl::pass_flags(touched, s + 1);
             d.drift = 1;
             d.ckb = 0.5 * c[s];
             d.ckt = s + 1 < M ? 0.5 * (c[s] + c[s + 1]) : 0.5 * c[s];
@@ -1906,7 +1907,6 @@ cl_status cl_ensemble_step(cl_ensemble* e, cl_integrator integ, int n, cl_observ
                                          hipGetErrorString(err != hipSuccess ? err : e2));
         }
         err = hipGraphInstantiate(&e->gexec, g, nullptr, nullptr, 0);
-            d.flags = cl::pass_flags(touched, s + 1);
         hipGraphDestroy(g);
         if (err != hipSuccess) {
             e->gexec = nullptr;
@@ -2001,6 +2001,7 @@ cl_status cl_ensemble_autotune(cl_ensemble* e, int reps, char* report, size_t ca
                 hipError_t r = hipSuccess;
                 for (int q = 0; q < 2 && r == hipSuccess; ++q) {
                     a.parity = q;
+                    a.flags = cl::pass_flags(ens_bytes(e), q);
                     r = cl::launch_ensemble_pass(a, e->prec, e->nf, e->grid, e->maxry, e->stream);
                 }
                 return r;
@@ -2021,7 +2022,6 @@ cl_status cl_ensemble_autotune(cl_ensemble* e, int reps, char* report, size_t ca
             std::snprintf(item, sizeof item, "%s{\"item_sites\":%d,\"two_rows\":%s,\"us\":%.2f}", first ? "" : ",",
                           sites, rows ? "true" : "false", ms * 1e3);
             js += item;
-                    a.flags = cl::pass_flags(ens_bytes(e), q);
             first = false;
             if (best_ms < 0.0f || ms < best_ms) {
                 best_ms = ms;

@@ -860,21 +860,23 @@ __device__ __forceinline__ void march_tile(const TileJob& J, unsigned char* smem
     }
 }
 
+// XCD-aware order: consecutive workgroup ids land on different XCDs (round
+// robin over 8), so give XCD k a contiguous range of tiles; its co-resident
+// workgroups then share halos in their L2.
+__device__ __forceinline__ int xcd_order(int bid, int nblocks) {
+    const int per = nblocks / 8, rem = nblocks % 8;
+    const int xcd = bid % 8, slot = bid / 8;
+    if (per == 0) return bid;
+    return (xcd < rem ? xcd * (per + 1) : rem * (per + 1) + (xcd - rem) * per) + slot;
+}
+
 // NTB: the launch bound (256, or 512 for the tall one-row-per-thread tiles,
 // whose register footprint fits two waves per SIMD).
 template <typename T, int NF, int RY, int HI, int PD, int RK, int NTB, int NG = 0>
 __global__ __launch_bounds__(NTB) void lattice_pass(PassArgs A) {
     constexpr int NS = kSumsPerField * NF + 1;
     const int nblocks = A.nbz * A.nby * A.nbx;
-    // XCD-aware order: consecutive workgroup ids land on different XCDs
-    // (round robin over 8), so give XCD k a contiguous range of tiles; its
-    // co-resident workgroups then share y/z halos in their L2.
-    int bid = blockIdx.x;
-    {
-        const int per = nblocks / 8, rem = nblocks % 8;
-        const int xcd = bid % 8, slot = bid / 8;
-        if (per > 0) bid = (xcd < rem ? xcd * (per + 1) : rem * (per + 1) + (xcd - rem) * per) + slot;
-    }
+    const int bid = xcd_order(blockIdx.x, nblocks);
     TileJob J;
     J.in = A.in;
     J.out = A.out;
@@ -1076,8 +1078,6 @@ bool finalize_tile(Tile& t, int N, cl_precision prec) {
     return true;
 }
 
-Tile default_tile(int N, cl_precision prec, int nf) {
-    const int V = prec == CL_FP32 ? 4 : 2;
 // x-planes a workgroup marches over: the divisor of N with the cheapest
 // schedule, counted in plane times -- rounds of workgroups over the CUs
 // (`per_round` run at a time), each paying its planes and about eight more
@@ -1109,11 +1109,13 @@ int march_length(int N, int tiles, int per_round) {
 // FP64 8.9 / 11.1, two fields 64^3 FP32 14.9 / 18.0, two fields 128^3 FP32
 // 24.2 / 30.9, two fields 256^3 FP32 99.7 / 108.9, one field 384^3 FP64
 // 344 / 382, two fields 512^3 FP32 721 / 798 (with the cache policy above).
-    Tile t;
-    t.TZ = N < 64 * V ? N : 64 * V;
+Tile default_tile(int N, cl_precision prec, int nf) {
+    const int V = prec == CL_FP32 ? 4 : 2;
     const size_t sites = static_cast<size_t>(N) * N * N;
     const size_t touched = 4 * nf * sites * (prec == CL_FP32 ? 4 : 8);
     const int threads = sites / V <= 32768 ? 64 : sites / V <= 131072 ? 128 : touched <= 2 * kMallBytes ? 256 : 512;
+    Tile t;
+    t.TZ = N < 64 * V ? N : 64 * V;
     const int BZ = t.TZ / V;
     t.RY = 1;
     int TY = threads / BZ;
@@ -1541,14 +1543,19 @@ __global__ __launch_bounds__(256) void lowdim_pass(PassArgs A) {
 // rows x-1, x, x+1 and pi of x, x+1 in registers, with the loads of row x+2
 // in flight, so a row leaves HBM about once (the z-neighbours of a group
 // come from the caches).  Items are dealt z-fastest, so a wave's loads are
-// contiguous.  Sums, scalar step and writes as in lowdim_pass.
+// contiguous, and an XCD takes neighbouring chunks of rows, which march
+// towards each other's shared rows together; odd passes march the other way
+// (kPassReverse).  Sums, scalar step and writes as in lowdim_pass.  Bound by
+// HBM: 4096^2, two fields, FP32 (536 MB per pass) 105 us = 5.1 TB/s; 131 us
+// with every chunk marching up, ordinary stores and no XCD order (117 us
+// where the two buffers happened to lie well).
 template <typename T, int NF>
 __global__ __launch_bounds__(256) void lowdim2_march(PassArgs A) {
     constexpr int NS = kSumsPerField * NF + 1;
     constexpr int V = VecOf<T>::V;
     const int NT = 256;
     const int nblocks = gridDim.x;
-    const int bid = blockIdx.x;
+    const int bid = xcd_order(blockIdx.x, nblocks);
     __shared__ Scal s_sc;
     __shared__ double tot[kMaxSums];
     {
@@ -1580,6 +1587,7 @@ __global__ __launch_bounds__(256) void lowdim2_march(PassArgs A) {
     const T qlam[2] = {T(0.25) * lam[0], T(0.25) * lam[1]};
     const T hg2 = T(0.5) * g2;
     const int N = A.N, CX = A.CX;
+    const bool nt_store = A.flags & kPassNtStore;
     const int per_row = N / V;
     const size_t rs = static_cast<size_t>(2 * NF) * N;
     const T* in = static_cast<const T*>(A.in);
@@ -1622,28 +1630,33 @@ __global__ __launch_bounds__(256) void lowdim2_march(PassArgs A) {
     const long items = static_cast<long>(per_row) * (N / CX);
     for (long it = static_cast<long>(bid) * NT + threadIdx.x; it < items; it += static_cast<long>(nblocks) * NT) {
         const int zc = static_cast<int>(it % per_row) * V;
-        const int x0 = static_cast<int>(it / per_row) * CX;
+        const int chunk = static_cast<int>(it / per_row);
+        const int x0 = chunk * CX;
+        // neighbouring chunks march in opposite directions, so that they
+        // reach the rows that both read at the same time
+        const bool rev = ((A.flags & kPassReverse) != 0) != (chunk & 1);
+        auto xof = [&](int k) { return rev ? x0 + CX - 1 - k : x0 + k; };
         Row ra, rb;
         Drift dprev, dcur, dnxt;
         T pcur[NF][V], pnxt[NF][V];
-        load_row(ra, x0 - 1, zc);
-        load_row(rb, x0, zc);
+        load_row(ra, xof(-1), zc);
+        load_row(rb, xof(0), zc);
         drift(ra, dprev);
         drift(rb, dcur);
 #pragma unroll
         for (int j = 0; j < NF; ++j)
 #pragma unroll
             for (int v = 0; v < V; ++v) pcur[j][v] = rb.p[j][v];
-        load_row(ra, x0 + 1, zc);
+        load_row(ra, xof(1), zc);
         for (int i = 0; i < CX; ++i) {
-            const int x = x0 + i;
+            const int x = xof(i);
             // row x+1 arrives (ra), the loads of row x+2 go out (rb)
             drift(ra, dnxt);
 #pragma unroll
             for (int j = 0; j < NF; ++j)
 #pragma unroll
                 for (int v = 0; v < V; ++v) pnxt[j][v] = ra.p[j][v];
-            if (i + 1 < CX) load_row(rb, x + 2, zc);
+            if (i + 1 < CX) load_row(rb, xof(i + 2), zc);
             T part[NS];
 #pragma unroll
             for (int q = 0; q < NS; ++q) part[q] = T(0);
@@ -1669,8 +1682,8 @@ __global__ __launch_bounds__(256) void lowdim2_march(PassArgs A) {
                     const T fc = fs[j];
                     const T zm = v == 0 ? dcur.zm[j] : dcur.f[j][v - 1];
                     const T zp = v == V - 1 ? dcur.zp[j] : dcur.f[j][v + 1];
-                    const T xm = dprev.f[j][v], xp = dnxt.f[j][v];
-                    const T nb = (xm + xp) + (zm + zp);
+                    const T xp = rev ? dprev.f[j][v] : dnxt.f[j][v];
+                    const T nb = (dprev.f[j][v] + dnxt.f[j][v]) + (zm + zp);
                     const T F = fmad(kL, fmad(T(-4), fc, nb), -(kV * dV[j]));
                     const T p0 = pcur[j][v];
                     const T p1 = fmad(kt, F, p0);
@@ -1689,8 +1702,13 @@ __global__ __launch_bounds__(256) void lowdim2_march(PassArgs A) {
                 const size_t row = static_cast<size_t>(x) * rs;
 #pragma unroll
                 for (int j = 0; j < NF; ++j) {
-                    vstore(out + row + static_cast<size_t>(j) * N + zc, dcur.f[j]);
-                    vstore(out + row + static_cast<size_t>(NF + j) * N + zc, pnew[j]);
+                    if (nt_store) {
+                        vstore_nt(out + row + static_cast<size_t>(j) * N + zc, dcur.f[j]);
+                        vstore_nt(out + row + static_cast<size_t>(NF + j) * N + zc, pnew[j]);
+                    } else {
+                        vstore(out + row + static_cast<size_t>(j) * N + zc, dcur.f[j]);
+                        vstore(out + row + static_cast<size_t>(NF + j) * N + zc, pnew[j]);
+                    }
                 }
             }
 #pragma unroll
