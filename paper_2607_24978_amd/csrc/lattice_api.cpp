@@ -96,10 +96,23 @@ bool valid_N(int N, cl_precision prec) {
     return pow2 || (N % big == 0);
 }
 
+// Tile of a pass that only reduces.  It stores nothing, so twice the
+// workgroups at half the march hide more of its loads: 256^3 two fields FP32
+// 61 us against 78, 512^3 373 against 420 (with at most kTunedPassBlocks of
+// them, and marches of 16 planes or more, whose first loads stay cheap).
+Tile reduce_tile(const cl_lattice* h) {
+    Tile t = h->tile;
+    if (h->dim == 3 && !h->ng && t.CX >= 32 && t.CX % 2 == 0 && 2 * t.nblocks() <= cl::kTunedPassBlocks) {
+        t.CX /= 2;
+        cl::finalize_tile(t, h->N, h->prec);
+    }
+    return t;
+}
+
 // Two halves of nsums * nblocks doubles: consecutive passes alternate, as a
 // pass reads the sums of the one before while writing its own.
 cl_status ensure_partials(cl_lattice* h, int nblocks = 0) {
-    if (nblocks <= 0) nblocks = h->tile.nblocks();
+    if (nblocks <= 0) nblocks = std::max(h->tile.nblocks(), reduce_tile(h).nblocks());
     const size_t need = 2 * static_cast<size_t>(cl::nsums(h->nf)) * nblocks;
     if (need <= h->partials_cap) return CL_OK;
     if (h->partials) hipFree(h->partials);
@@ -124,18 +137,18 @@ cl_status ensure_obs(cl_lattice* h, int n) {
     return CL_OK;
 }
 
-PassArgs base_args(cl_lattice* h, int in) {
+PassArgs base_args(cl_lattice* h, int in, const Tile& t) {
     PassArgs a{};
     a.in = h->buf[in];
     a.out = h->buf[in ^ 1];
     a.flags = 0;
     a.N = h->N;
-    a.TZ = h->tile.TZ;
-    a.TY = h->tile.TY;
-    a.CX = h->tile.CX;
-    a.nbz = h->tile.nbz;
-    a.nby = h->tile.nby;
-    a.nbx = h->tile.nbx;
+    a.TZ = t.TZ;
+    a.TY = t.TY;
+    a.CX = t.CX;
+    a.nbz = t.nbz;
+    a.nby = t.nby;
+    a.nbx = t.nbx;
     a.sc_in = h->sc;
     a.sc_out = nullptr;
     a.partials = h->partials;
@@ -155,6 +168,8 @@ PassArgs base_args(cl_lattice* h, int in) {
     return a;
 }
 
+PassArgs base_args(cl_lattice* h, int in) { return base_args(h, in, h->tile); }
+
 cl::Work handle_work(cl_lattice* h) {
     return cl::Work{h->partials, h->partials_cap / 2, h->scb, h->obs, h->obs_cap};
 }
@@ -167,17 +182,19 @@ cl::Work handle_work(cl_lattice* h) {
 struct PassSeq {
     cl_lattice* h;
     cl::Work w;
+    Tile tile;  // of every pass of the sequence
     int p = 0;
     PassArgs prev{};
-    explicit PassSeq(cl_lattice* hh) : h(hh), w(handle_work(hh)) {}
-    PassSeq(cl_lattice* hh, const cl::Work& ww) : h(hh), w(ww) {}
+    explicit PassSeq(cl_lattice* hh) : PassSeq(hh, hh->tile) {}
+    PassSeq(cl_lattice* hh, const Tile& t) : h(hh), w(handle_work(hh)), tile(t) {}
+    PassSeq(cl_lattice* hh, const cl::Work& ww) : h(hh), w(ww), tile(hh->tile) {}
     double* part(int q) const { return w.partials + q * w.half; }
     const Scal* scal_before(int q) const { return q == 0 ? h->sc : w.scb + (q & 1); }
     void chain(PassArgs& a) const {
         a.has_prev = 1;
         a.sc_in = scal_before(p - 1);
         a.prev_partials = part((p - 1) & 1);
-        a.prev_nslots = h->tile.nblocks();
+        a.prev_nslots = tile.nblocks();
         a.pkt = prev.kt;
         a.pkb = prev.kb;
         a.phn = prev.h_next;
@@ -204,7 +221,7 @@ struct PassSeq {
             chain(a);
             a.sc_out = w.scb + (p & 1);
         }
-        const hipError_t e = cl::launch_pass(a, h->tile, h->prec, h->stream);
+        const hipError_t e = cl::launch_pass(a, tile, h->prec, h->stream);
         prev = a;
         ++p;
         return e;
@@ -214,7 +231,7 @@ struct PassSeq {
         PassArgs f = prev;
         chain(f);
         f.sc_out = h->sc;
-        return cl::launch_finish(f, h->tile, h->nf, h->stream);
+        return cl::launch_finish(f, tile, h->nf, h->stream);
     }
 };
 
@@ -558,14 +575,15 @@ cl_status init_scalars(cl_lattice* h, double a, double b, double eta, const doub
 cl_status reduce_pass(cl_lattice* h, cl_observables* out, Scal* sc_out = nullptr) {
     cl_status st = ensure_obs(h, 1);
     if (st) return st;
-    PassArgs r = base_args(h, h->cur);
+    const Tile t = reduce_tile(h);
+    PassArgs r = base_args(h, h->cur, t);
     r.drift = 0;
     r.write_out = 0;
     r.kt = 0.0;
     r.kb = 0.0;
     r.h_next = 0.0;
     r.rec = 0;
-    PassSeq seq(h);
+    PassSeq seq(h, t);
     HIPCHECK(h, seq.launch(r));
     HIPCHECK(h, seq.close());
     HIPCHECK(h, hipMemcpyAsync(out, h->obs, sizeof(cl_observables), hipMemcpyDeviceToHost, h->stream));
