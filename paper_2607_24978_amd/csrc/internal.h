@@ -260,6 +260,7 @@ struct PropModeArgs {
                            // lattices, else FP64 (workspace of 16 doubles per entry)
     const uint32_t* triples;  // prop_triples(N) on the device
     size_t ntriples;
+    const void* tw;        // exp(-2 pi i k / N), k < N / 2, in the state's precision
 };
 // Entries of the transfer-matrix table: sorted triples i0 <= i1 <= i2 of
 // folded mode indices (each in [0, N/2]), and the list of them in table
@@ -269,18 +270,22 @@ std::vector<uint32_t> prop_triples(int N);
 // Packing + forward z pass; inverse z pass + unpacking into `out`.
 hipError_t launch_prop_pack_fftz(const PropZArgs& a, bool fp32, hipStream_t s);
 hipError_t launch_prop_ifftz_unpack(const PropZArgs& a, bool fp32, hipStream_t s);
+// Whether launch_prop_modes also runs the x transforms before and after the
+// modes (out of place: its `in` then holds the z and y transforms, its `out`
+// what the inverse y pass takes).
+bool prop_modes_with_x(int N, bool fp32);
 // Transfer matrices (FP64) and their application to every mode; fp32: the
 // arrays hold float2 values (converted to FP64 for the product).
 hipError_t launch_prop_modes(const PropModeArgs& a, bool fp32, hipStream_t s);
 hipError_t launch_init_scalars(Scal* sc, double a, double b, double eta, const Phys& ph,
                                const double* shift, hipStream_t s);
 // Default tile for a lattice; valid for every N accepted by cl_create.
+int march_length(int N, int tiles, int per_round);
 Tile default_tile(int N, cl_precision prec, int nf);
 // Fill nbz/nby/nbx and check that the tile divides the lattice and fits the
 // kernel's limits.  Returns false if not.
 bool finalize_tile(Tile& t, int N, cl_precision prec);
 // LDS of a pass for `arrays` stencil arrays (the fields, plus the tensor
-int march_length(int N, int tiles, int per_round);
 // components when gravitational waves are on).
 size_t pass_lds_bytes(const Tile& t, cl_precision prec, int arrays);
 // All valid tiles the autotuner tries for a lattice.
@@ -350,7 +355,6 @@ struct cl_lattice {
     unsigned long long* spec_counts = nullptr;  // the last pass's atomics on both were slower in one)
     double* spec_host = nullptr;        // pinned host copy: spec_cap sums, then spec_cap counts
     int spec_cap = 0;
-    int pass_flags = 1;                 // nontemporal stores
     int cur = 0;
     cl::Scal* sc = nullptr;
     double* partials = nullptr;  // two halves, used by alternate passes

@@ -20,6 +20,7 @@
 // live in registers.  Each thread owns V consecutive z values (16-byte
 // vector loads and stores) in RY rows.
 #include "internal.h"
+#include "xcd_order.h"
 
 #include <hip/hip_runtime.h>
 #include <cmath>
@@ -858,16 +859,6 @@ __device__ __forceinline__ void march_tile(const TileJob& J, unsigned char* smem
             if (i + s_ < CX) body(Set{}, HSet{}, i + s_);
         });
     }
-}
-
-// XCD-aware order: consecutive workgroup ids land on different XCDs (round
-// robin over 8), so give XCD k a contiguous range of tiles; its co-resident
-// workgroups then share halos in their L2.
-__device__ __forceinline__ int xcd_order(int bid, int nblocks) {
-    const int per = nblocks / 8, rem = nblocks % 8;
-    const int xcd = bid % 8, slot = bid / 8;
-    if (per == 0) return bid;
-    return (xcd < rem ? xcd * (per + 1) : rem * (per + 1) + (xcd - rem) * per) + slot;
 }
 
 // NTB: the launch bound (256, or 512 for the tall one-row-per-thread tiles,

@@ -1131,6 +1131,8 @@ cl_status cl_surrogate_advance(cl_lattice* h, cl_surrogate* s, cl_integrator fal
     const bool fp32 = h->prec == CL_FP32;
     // twiddles of the fused z passes, in the lattice's precision
     const void* const twz = fp32 ? static_cast<const void*>(s->tw32) : static_cast<const void*>(tw);
+    // the x transforms run with the modes where that pass is built
+    const bool with_x = cl::prop_modes_with_x(N, fp32);
     if (!s->jump_obs &&
         hipHostMalloc(reinterpret_cast<void**>(&s->jump_obs), sizeof(cl_surrogate::JumpObs)) != hipSuccess) {
         s->jump_obs = nullptr;
@@ -1182,8 +1184,8 @@ cl_status cl_surrogate_advance(cl_lattice* h, cl_surrogate* s, cl_integrator fal
             }
             for (int q = 0; q < h->nf; ++q) pk.z[q] = s->pz[q];
             SHIP(cl::launch_prop_pack_fftz(pk, fp32, h->stream));
-            for (int q = 0; q < h->nf; ++q)
-                for (int axis = 1; axis < 3; ++axis) SHIP(prop_fft(s, q, true, tw, N, axis, fp32, false, h->stream));
+            for (int q = h->nf - 1; q >= 0; --q)  // the array written last first: it is still cached
+                for (int axis = 1; axis < (with_x ? 2 : 3); ++axis) SHIP(prop_fft(s, q, true, tw, N, axis, fp32, false, h->stream));
         }
         // predictor: homogeneous modes and background over the jump, in FP64
         double f[2] = {o.mean[0], o.mean[1]}, pm[2] = {sc.mean_p[0], sc.mean_p[1]}, var[2] = {o.var[0], o.var[1]};
@@ -1217,9 +1219,10 @@ cl_status cl_surrogate_advance(cl_lattice* h, cl_surrogate* s, cl_integrator fal
             pmd.table = s->ptable;
             pmd.triples = s->ptriples;
             pmd.ntriples = cl::prop_table_entries(N);
+            pmd.tw = twz;
             SHIP(cl::launch_prop_modes(pmd, fp32, h->stream));
             for (int q = 0; q < h->nf; ++q)
-                for (int axis = 2; axis >= 1; --axis) SHIP(prop_fft(s, q, false, tw, N, axis, fp32, true, h->stream));
+                for (int axis = with_x ? 1 : 2; axis >= 1; --axis) SHIP(prop_fft(s, q, false, tw, N, axis, fp32, true, h->stream));
             cl::PropZArgs pu{};
             pu.out = dst;
             pu.N = N;
