@@ -16,6 +16,7 @@
 #define CL_FFT_REG_H
 
 #include "fft_lds.h"
+#include "static_for.h"
 
 #include <hip/hip_runtime.h>
 #include <type_traits>
@@ -126,16 +127,6 @@ __device__ __forceinline__ void reg_second(V2 (&x)[RegPlan<N>::R1], const V2* bu
                 for (int j = q; j < P::R2; j += 2 * h) butterfly(y[j], y[j + h], cmul(y[j + h], w));
             }
         }
-    }
-}
-
-// f(integral_constant<int, 0>) .. f(integral_constant<int, E - 1>): a loop over
-// registers that is unrolled whatever its body.
-template <int E, int B = 0, typename F>
-__device__ __forceinline__ void static_for(F&& f) {
-    if constexpr (B < E) {
-        f(std::integral_constant<int, B>{});
-        static_for<E, B + 1>(f);
     }
 }
 

@@ -15,8 +15,11 @@
 // B = inputs (n = site), so each lane ends with 4 consecutive output
 // channels of one site.
 #include "surrogate.h"
+#include "static_for.h"
+#include "xcd_order.h"
 
 #include <hip/hip_runtime.h>
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 
@@ -207,220 +210,330 @@ __global__ __launch_bounds__(256) void conv_fwd(ConvArgs a) {
     }
 }
 
-// Register-blocked forward for 32 input channels and NB 16-wide output blocks
-// (the hidden layers, the last layer, and the input gradient through the
-// hidden layers).  A workgroup takes 4 x-planes
-// (one per wave) x RY y-rows x 16 z-sites; the input block with its halo
-// (6 x (RY+2) x 18 sites x 32 channels) is staged once in LDS.  For each dx
-// the wave holds the 9 (dy, dz) weight fragments of its output blocks in
-// registers, and every input fragment it reads from LDS feeds the
-// three output rows it is a neighbour of.
-template <int RY, int NB>
-__global__ __launch_bounds__(256, 2) void conv32_fwd_tiled(ConvArgs a) {
-    constexpr int ZR = 18, YR = RY + 2, PL = 6;
-    __shared__ __align__(16) uint16_t tin[PL * YR * ZR * 32];
-    const uint16_t* __restrict__ in = reinterpret_cast<const uint16_t*>(a.in);
-    const uint16_t* __restrict__ wg = reinterpret_cast<const uint16_t*>(a.w);
-    const int N = a.N;
-    const int nzt = N / 16, nyt = N / RY;
-    int t = blockIdx.x;
-    const int tz = t % nzt;
-    t /= nzt;
-    const int ty = t % nyt;
-    const int tx = t / nyt;
-    const int x0 = tx * 4, y0 = ty * RY, z0 = tz * 16;
-    constexpr int CHUNKS = PL * YR * ZR * 4;  // 16-byte chunks (8 channels)
-    constexpr int ITER = (CHUNKS + 255) / 256;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int n = lane & 15, g = lane >> 4;
-    // the weights of dx = 0 first: they do not depend on the block and are in
-    // flight with its loads
-    bf16x8 wa[9][NB];
+// What the tiled convolutions make of their FP32 sums plus bias v: z_out = v
+// (kEpiZ), a_out = GELU(v) (kEpiGelu), that and zh_out = v (kEpiGeluKeep, when
+// the backward pass follows), or a_out = v GELU'(gz) (kEpiGeluGrad).
+enum ConvEpilogue { kEpiZ, kEpiGelu, kEpiGeluKeep, kEpiGeluGrad };
+
+// Four outputs of one lane: a_out of the modes that write one.
+template <int MODE>
+__device__ __forceinline__ uint2 epilogue4(const float* v, uint2 gz) {
+    float h[4], zv[4];
+    if constexpr (MODE == kEpiGeluGrad) unpack4(gz, zv);
 #pragma unroll
-    for (int j = 0; j < 9; ++j)
-#pragma unroll
-        for (int b = 0; b < NB; ++b) wa[j][b] = load8(wg + static_cast<size_t>(j * NB * 16 + 16 * b + n) * 32 + 8 * g);
-    // all loads of the tile first, then all LDS stores: the loads are in
-    // flight together instead of one round trip per chunk
-    u32x4 v[ITER];
-    if (x0 >= 1 && x0 + PL - 1 <= N && y0 >= 1 && y0 + YR - 1 <= N && z0 >= 1 && z0 + ZR - 1 <= N) {
-        // no periodic image in the block: offsets from its first site
-        const uint16_t* base = in + static_cast<size_t>(((x0 - 1) * N + y0 - 1) * N + z0 - 1) * 32;
-#pragma unroll
-        for (int k = 0; k < ITER; ++k) {
-            // past the last chunk a thread re-reads it (in bounds) and stores nothing
-            const int i = min(static_cast<int>(threadIdx.x) + k * 256, CHUNKS - 1);
-            const int r = i >> 2, zi = r % ZR, yi = (r / ZR) % YR, pi = r / (ZR * YR);
-            v[k] = *reinterpret_cast<const u32x4*>(base + ((pi * N + yi) * N + zi) * 32 + (i & 3) * 8);
-        }
-    } else {
-#pragma unroll
-        for (int k = 0; k < ITER; ++k) {
-            const int i = min(static_cast<int>(threadIdx.x) + k * 256, CHUNKS - 1);
-            const int c4 = i & 3;
-            int r = i >> 2;
-            const int zi = r % ZR;
-            r /= ZR;
-            const int yi = r % YR, pi = r / YR;
-            int xx = x0 - 1 + pi, yy = y0 - 1 + yi, zz = z0 - 1 + zi;
-            xx = xx < 0 ? xx + N : (xx >= N ? xx - N : xx);
-            yy = yy < 0 ? yy + N : (yy >= N ? yy - N : yy);
-            zz = zz < 0 ? zz + N : (zz >= N ? zz - N : zz);
-            v[k] = *reinterpret_cast<const u32x4*>(in + static_cast<size_t>((xx * N + yy) * N + zz) * 32 + c4 * 8);
-        }
-    }
-    __builtin_amdgcn_sched_barrier(0);  // every load issued before the first store waits
-#pragma unroll
-    for (int k = 0; k < ITER; ++k) {
-        const int i = threadIdx.x + k * 256;
-        if (i < CHUNKS) *reinterpret_cast<u32x4*>(tin + static_cast<size_t>(i) * 8) = v[k];
-    }
-    __syncthreads();
-    uint2 zg[RY][NB];
-    f32x4 acc[RY][NB];
-#pragma unroll
-    for (int r = 0; r < RY; ++r)
-#pragma unroll
-        for (int b = 0; b < NB; ++b) acc[r][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int dx = 0; dx < 3; ++dx) {
-        // the next dx's weights load during this dx's MFMAs
-        bf16x8 wn[9][NB];
-        if (dx < 2) {
-#pragma unroll
-            for (int j = 0; j < 9; ++j)
-#pragma unroll
-                for (int b = 0; b < NB; ++b)
-                    wn[j][b] = load8(wg + static_cast<size_t>(((dx + 1) * 9 + j) * NB * 16 + 16 * b + n) * 32 + 8 * g);
-        } else if (a.gz) {
-            // the pre-activations the input gradient's epilogue needs (the
-            // registers of the weight prefetch are free in the last dx)
-#pragma unroll
-            for (int r = 0; r < RY; ++r)
-#pragma unroll
-                for (int b = 0; b < NB; ++b)
-                    zg[r][b] = *reinterpret_cast<const uint2*>(reinterpret_cast<const uint16_t*>(a.gz) +
-                                                               static_cast<size_t>(((x0 + w) * N + y0 + r) * N + z0 + n) *
-                                                                   a.gz_stride + 16 * b + 4 * g);
-        }
-        __builtin_amdgcn_sched_barrier(0);  // keep them ahead of the MFMAs
-        const uint16_t* pl = tin + (w + dx) * YR * ZR * 32;
-#pragma unroll
-        for (int yi = 0; yi < YR; ++yi)
-#pragma unroll
-            for (int dz = 0; dz < 3; ++dz) {
-                const bf16x8 xb = load8(pl + (yi * ZR + n + dz) * 32 + 8 * g);
-#pragma unroll
-                for (int dy = 0; dy < 3; ++dy) {
-                    const int r = yi - dy;  // output row fed by input row yi at this dy
-                    if (r < 0 || r >= RY) continue;
-#pragma unroll
-                    for (int b = 0; b < NB; ++b)
-                        acc[r][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa[dy * 3 + dz][b], xb, acc[r][b], 0, 0, 0);
-                }
-            }
-        if (dx < 2) {
-#pragma unroll
-            for (int j = 0; j < 9; ++j)
-#pragma unroll
-                for (int b = 0; b < NB; ++b) wa[j][b] = wn[j][b];
-        }
-    }
-    // this lane's bias values, all loaded before the first store (which the
-    // compiler cannot prove does not alias them)
-    float bias[NB][4];
-#pragma unroll
-    for (int b = 0; b < NB; ++b)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int c = 16 * b + 4 * g + q;
-            bias[b][q] = (a.bias && c < a.cout) ? a.bias[c] : 0.f;
-        }
-    // epilogue: every output value first, then all stores back to back (each
-    // from registers of its own, so that no store waits for an earlier one)
-    const int x = x0 + w;
-    f32x4 zf[RY][NB];
-    uint2 zh[RY][NB], ao[RY][NB];
-#pragma unroll
-    for (int r = 0; r < RY; ++r)
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            float v[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) v[q] = acc[r][b][q] + bias[b][q];
-            zf[r][b] = f32x4{v[0], v[1], v[2], v[3]};
-            if (a.zh_out) zh[r][b] = cvt4(v);
-            if (a.a_out) {
-                float h[4];
-                if (a.gz) {
-                    float zv[4];
-                    unpack4(zg[r][b], zv);
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) h[q] = v[q] * gelu_grad(zv[q]);
-                } else if (a.gelu) {
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) h[q] = gelu(v[q]);
-                } else {
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) h[q] = v[q];
-                }
-                ao[r][b] = cvt4(h);
-            }
-        }
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int r = 0; r < RY; ++r) {
-        const size_t site = static_cast<size_t>((x * N + y0 + r) * N + z0 + n);
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            const int c0 = 16 * b + 4 * g;
-            if (c0 >= a.cout) continue;
-            if (a.z_out) *reinterpret_cast<f32x4*>(a.z_out + site * a.z_stride + c0) = zf[r][b];
-            if (a.zh_out) *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.zh_out) + site * a.zh_stride + c0) = zh[r][b];
-            if (a.a_out) *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.a_out) + site * a.a_stride + c0) = ao[r][b];
-        }
-    }
+    for (int q = 0; q < 4; ++q) h[q] = MODE == kEpiGeluGrad ? v[q] * gelu_grad(zv[q]) : gelu(v[q]);
+    return cvt4(h);
 }
 
-// The same blocking for 8 input channels and 32 outputs (the first layer, and
-// the input gradient through the last one): one K = 32 step packs the
-// 8 channels of 4 stencil offsets, lane group g taking offset 4s + g, so the
-// whole weight set (7 steps x 2 output blocks) stays in registers.
-template <int RY>
-__global__ __launch_bounds__(256, 2) void conv8_fwd_tiled(ConvArgs a) {
+// One stage of the epilogue of four outputs of a lane, in kEpiStages pieces so
+// that the march below can put a piece between its matrix products.  The
+// arithmetic is that of gelu and gelu_grad, operation for operation.
+struct EpiState {
+    float x[4], t[4], p[4], d[4];
+};
+constexpr int kEpiStages = 11;
+
+template <int MODE, int S>
+__device__ __forceinline__ void epi_stage(EpiState& e, const f32x4 v, uint2 gz, uint2& out) {
+    constexpr float kLog2e = 1.4426950408889634f;
+    constexpr float kP[10] = {0.17087277f, -0.82215223f, 1.48851587f, -1.13520398f, 0.27886807f,
+                              -0.18628806f, 0.09678418f, 0.37409196f, 1.00002368f, -1.26551223f};
+    float z[4] = {v[0], v[1], v[2], v[3]};
+    if constexpr (MODE == kEpiGeluGrad) unpack4(gz, z);
+    if constexpr (MODE == kEpiZ) return;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        if constexpr (S == 0) {
+            e.x[q] = fabsf(z[q]) * 0.70710678118654752f;
+            e.t[q] = fmaf(0.5f, e.x[q], 1.0f);
+        } else if constexpr (S == 1) {
+            e.t[q] = __builtin_amdgcn_rcpf(e.t[q]);
+            e.p[q] = kP[0];
+        } else if constexpr (S <= 5) {
+            e.p[q] = fmaf(e.p[q], e.t[q], kP[2 * S - 3]);
+            e.p[q] = fmaf(e.p[q], e.t[q], kP[2 * S - 2]);
+        } else if constexpr (S == 6) {
+            e.p[q] = fmaf(e.p[q], e.t[q], kP[9]);
+            e.x[q] = -e.x[q] * e.x[q];
+            if constexpr (MODE == kEpiGeluGrad) e.d[q] = e.x[q] * kLog2e;
+        } else if constexpr (S == 7) {
+            e.p[q] = (e.x[q] + e.p[q]) * kLog2e;
+            if constexpr (MODE == kEpiGeluGrad) e.d[q] = __builtin_amdgcn_exp2f(e.d[q]);
+        } else if constexpr (S == 8) {
+            e.p[q] = __builtin_amdgcn_exp2f(e.p[q]);
+        } else if constexpr (S == 9) {
+            e.p[q] = 0.5f * e.t[q] * e.p[q];
+            if constexpr (MODE == kEpiGeluGrad) e.d[q] = z[q] * (0.39894228040143268f * e.d[q]);
+        } else {
+            const float c = z[q] >= 0.f ? 1.0f - e.p[q] : e.p[q];
+            e.p[q] = MODE == kEpiGeluGrad ? v[q] * (c + e.d[q]) : z[q] * c;
+        }
+    }
+    if constexpr (S == kEpiStages - 1) out = cvt4(e.p);
+}
+
+// Forward for 32 input channels and NB 16-wide output blocks (the hidden
+// layers, the last layer, and the input gradient through the hidden layers).
+//
+// A workgroup of eight waves owns a column of RY y-rows x 16 z-sites and
+// marches along x, four output planes a step.  The planes with their halo
+// ((RY+2) x 18 sites x 32 channels, 11.5 KB) live in a ring of ten in LDS: six
+// are read in a step while the four of the next come from memory through
+// registers, one barrier a step.  Two waves share each output plane: with two
+// output blocks each takes one of them, with one block each takes half the
+// rows (RW rows).  A wave keeps all 27 weight fragments of its block in
+// registers for the whole march, and every input fragment it reads from LDS
+// feeds the three output rows it is a neighbour of; chunks of a site are
+// rotated by zi/4 in LDS.  The epilogue of a step (GELU: about 20 vector
+// operations and two transcendental ones per output, as long as the matrix
+// products themselves) is cut into pieces that go between the products of the
+// next step, so that the two units work at the same time within a wave.
+//
+// Bound: the matrix cores at the rate they sustain here.  32 -> 32 channels on
+// 128^3 with GELU: 130 us, 900 TFLOP/s of the 1160 TFLOP/s a large library
+// product reaches; without the epilogue and memory traffic the same loop takes
+// 73 us, without the products 65 us.  A kernel that staged one 4 x 8 x 16
+// tile, multiplied, then ran its epilogue took 171 us, with four waves per SIMD
+// instead of two still 165 us: its phases did not overlap.  32 -> 8 (NB = 1):
+// 79 us before, 57 us now.
+template <int RY, int NB, int MODE>
+__global__ __launch_bounds__(512, 2) void conv32_march(ConvArgs a, int L) {
+    static_assert(NB == 2 || MODE == kEpiZ, "only an epilogue that computes nothing has lanes without an output");
+    constexpr int ZR = 18, YR = RY + 2, RING = 10;
+    constexpr int PLANE = YR * ZR * 32;
+    constexpr int RW = NB == 2 ? RY : RY / 2;
+    __shared__ __align__(16) uint16_t tin[RING * PLANE + 8];  // and one chunk for the writes of threads without one
+    const uint16_t* __restrict__ in = reinterpret_cast<const uint16_t*>(a.in);
+    const int N = a.N;
+    const int nzt = N / 16, nyt = N / RY;
+    int t = xcd_order(blockIdx.x, gridDim.x);
+    const int z0 = (t % nzt) * 16;
+    t /= nzt;
+    const int y0 = (t % nyt) * RY;
+    int x0 = (t / nyt) * (4 * L);
+    const int steps = min(L, (N - x0) / 4);
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) & 3);
+    const int half = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
+    const int n = lane & 15, g = lane >> 4;
+    const int bs = NB == 2 ? half : 0;       // output block of this wave
+    const int r0 = NB == 2 ? 0 : half * RW;  // its first row in the tile
+    const uint16_t* __restrict__ wg = reinterpret_cast<const uint16_t*>(a.w) + (16 * bs + n) * 32 + 8 * g;
+    bf16x8 wa[27];
+#pragma unroll
+    for (int j = 0; j < 27; ++j) wa[j] = load8(wg + j * NB * 16 * 32);
+
+    // staging: a thread keeps its 16-byte chunk of the z row and walks the
+    // (plane, row) pairs, ROWS at a time
+    constexpr int RC = ZR * 4, ROWS = 512 / RC;
+    const int rr = threadIdx.x / RC, ch = threadIdx.x % RC;
+    const int zc = ch >> 2;
+    int zz = z0 - 1 + zc;
+    zz = zz < 0 ? zz + N : (zz >= N ? zz - N : zz);
+    const uint32_t zoff = static_cast<uint32_t>(zz * 64 + (ch & 3) * 16);
+    const int zslot = (zc * 4 + (((ch & 3) + (zc >> 2)) & 3)) * 8;
+    auto wrap = [N](int i) { return i < 0 ? i + N : (i >= N ? i - N : i); };
+    {
+        constexpr int NROW = 6 * YR, ITER = (NROW + ROWS - 1) / ROWS;
+        u32x4 v[ITER];
+#pragma unroll
+        for (int k = 0; k < ITER; ++k) {
+            // past the last row a thread re-reads it (in bounds) and stores nothing
+            const int row = min(rr + k * ROWS, NROW - 1), pi = row / YR, yi = row - pi * YR;
+            v[k] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(in) +
+                                                   static_cast<size_t>(wrap(x0 - 1 + pi) * N + wrap(y0 - 1 + yi)) * (N * 64) + zoff);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int k = 0; k < ITER; ++k) {
+            const int row = rr + k * ROWS;
+            if (rr < ROWS && row < NROW) *reinterpret_cast<u32x4*>(tin + row * (ZR * 32) + zslot) = v[k];
+        }
+    }
+    constexpr int NROW = 4 * YR, ITER = (NROW + ROWS - 1) / ROWS;
+    uint32_t loff[ITER];  // byte offset of a thread's chunks from the first of the four planes
+#pragma unroll
+    for (int k = 0; k < ITER; ++k) {
+        const int row = min(rr + k * ROWS, NROW - 1), pi = row / YR, yi = row - pi * YR;
+        loff[k] = static_cast<uint32_t>(pi * N + wrap(y0 - 1 + yi)) * static_cast<uint32_t>(N * 64) + zoff;
+    }
+    const int c0 = 16 * bs + 4 * g;
+    const bool on = c0 < a.cout;  // not a channel that only pads the block
+    float bias[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) bias[q] = a.bias && on ? a.bias[c0 + q] : 0.f;
+    uint32_t roff[3];  // of a lane's fragment in an LDS row, for each dz
+#pragma unroll
+    for (int dz = 0; dz < 3; ++dz) {
+        const int zi = n + dz;
+        roff[dz] = (zi * 4 + ((g + (zi >> 2)) & 3)) * 8 + r0 * ZR * 32;
+    }
+    f32x4 acc[RW], old[RW];
+    uint2 zg[RW];
+    int slot0 = 0;  // ring slot of plane x0 - 1
+    // weights and bias are here: else every step's waits, which have to hold for
+    // the first step too, would wait for that step's own loads and stores
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+
+    // Stores of row r of plane xo.  No branch on a run-time value around what the
+    // epilogue computes: the compiler would move all of its pieces into it.
+    auto finish = [&](auto R, uint2 o, int xo) {
+        constexpr int r = decltype(R)::value;
+        const size_t site = static_cast<size_t>((xo * N + y0 + r0 + r) * N + z0);
+        if constexpr (MODE == kEpiZ) {
+            if (on) *reinterpret_cast<f32x4*>(a.z_out + (site * a.z_stride + 16 * bs) + (n * a.z_stride + 4 * g)) = old[r];
+        } else {
+            if constexpr (MODE == kEpiGeluKeep) {
+                const float u[4] = {old[r][0], old[r][1], old[r][2], old[r][3]};
+                *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.zh_out) + (site * a.zh_stride + 16 * bs) +
+                                          (n * a.zh_stride + 4 * g)) = cvt4(u);
+            }
+            *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.a_out) + (site * a.a_stride + 16 * bs) +
+                                      (n * a.a_stride + 4 * g)) = o;
+        }
+    };
+    EpiState es;
+    uint2 eo;
+    // piece `i` of the epilogue of the previous step's rows
+    auto piece = [&](auto I, int xo) {
+        constexpr int i = decltype(I)::value;
+        if constexpr (i >= 0 && i < RW * kEpiStages) {
+            constexpr int r = i / kEpiStages, s = i % kEpiStages;
+            epi_stage<MODE, s>(es, old[r], zg[r], eo);
+            if constexpr (s == kEpiStages - 1) finish(std::integral_constant<int, r>{}, eo, xo);
+        }
+    };
+    auto products = [&](auto WithOld, int xo) {
+        constexpr int G = 9 * (RW + 2);  // (dx, yi, dz) groups, one input fragment each
+        constexpr int AHEAD = 2;
+        bf16x8 xb[AHEAD + 1];
+        const uint16_t* pl[3];
+#pragma unroll
+        for (int dx = 0; dx < 3; ++dx) {
+            int sl = slot0 + w + dx;
+            sl = sl >= RING ? sl - RING : sl;
+            pl[dx] = tin + sl * PLANE;
+        }
+        auto fetch = [&](auto GI) {
+            constexpr int gi = decltype(GI)::value;
+            if constexpr (gi < G) {
+                constexpr int dx = gi / (3 * (RW + 2)), yi = (gi / 3) % (RW + 2), dz = gi % 3;
+                xb[gi % (AHEAD + 1)] = load8(pl[dx] + roff[dz] + yi * ZR * 32);
+            }
+        };
+#pragma unroll
+        for (int r = 0; r < RW; ++r) acc[r] = f32x4{0.f, 0.f, 0.f, 0.f};
+        static_for<AHEAD>([&](auto GI) { fetch(GI); });
+        static_for<G>([&](auto GI) {
+            constexpr int gi = decltype(GI)::value;
+            constexpr int dx = gi / (3 * (RW + 2)), yi = (gi / 3) % (RW + 2), dz = gi % 3;
+            fetch(std::integral_constant<int, gi + AHEAD>{});
+#pragma unroll
+            for (int dy = 0; dy < 3; ++dy) {
+                const int r = yi - dy;  // output row fed by input row yi at this dy
+                if (r < 0 || r >= RW) continue;
+                acc[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa[dx * 9 + dy * 3 + dz], xb[gi % (AHEAD + 1)], acc[r], 0, 0, 0);
+            }
+            if constexpr (decltype(WithOld)::value) {
+                constexpr int first = G - RW * kEpiStages;
+                piece(std::integral_constant<int, gi - (first > 0 ? first : 0)>{}, xo);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+    // one step: its products, with the epilogue of the step before; the planes the
+    // next step adds to the ring are in flight meanwhile.  The first step has its
+    // own copy so that the waits of the others know how many stores follow a load.
+    const size_t box = static_cast<size_t>(N) * N * (N * 64);
+    auto step = [&](auto WithOld, bool more) {
+        u32x4 v[ITER];
+        if (more) {
+            const char* base = reinterpret_cast<const char*>(in) + static_cast<size_t>(x0 + 5) * N * (N * 64);
+            const size_t back = x0 + 8 == N ? box : 0;  // only the last plane can be a periodic image
+#pragma unroll
+            for (int k = 0; k < ITER; ++k) {
+                const bool last = (ROWS - 1 + k * ROWS) / YR >= 3 && rr + k * ROWS >= 3 * YR;
+                v[k] = *reinterpret_cast<const u32x4*>((last ? base - back : base) + loff[k]);
+            }
+        }
+        products(WithOld, x0 - 4 + w);
+#pragma unroll
+        for (int r = 0; r < RW; ++r)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) old[r][q] = acc[r][q] + bias[q];
+        if constexpr (MODE == kEpiGeluGrad) {
+#pragma unroll
+            for (int r = 0; r < RW; ++r)
+                zg[r] = *reinterpret_cast<const uint2*>(reinterpret_cast<const uint16_t*>(a.gz) +
+                                                        (static_cast<size_t>(((x0 + w) * N + y0 + r0 + r) * N + z0) * a.gz_stride + 16 * bs) +
+                                                        (n * a.gz_stride + 4 * g));
+        }
+        if (more) {
+#pragma unroll
+            for (int k = 0; k < ITER; ++k) {
+                const int row = rr + k * ROWS, pi = row / YR;
+                int sl = slot0 + 6 + pi;
+                sl = sl >= RING ? sl - RING : sl;
+                // every thread writes: a branch around it would make the next loads wait for this step's stores
+                const int at = sl * PLANE + (row - pi * YR) * (ZR * 32) + zslot;
+                *reinterpret_cast<u32x4*>(tin + (rr < ROWS && row < NROW ? at : RING * PLANE)) = v[k];
+            }
+            slot0 = slot0 + 4 >= RING ? slot0 + 4 - RING : slot0 + 4;
+            __syncthreads();
+        }
+    };
+    step(std::false_type{}, steps > 1);
+    for (int s = 1; s < steps; ++s) {
+        x0 += 4;
+        step(std::true_type{}, s + 1 < steps);
+    }
+    static_for<RW * kEpiStages>([&](auto I) { piece(I, x0 + w); });
+}
+
+// Forward for 8 input channels and 32 outputs (the first layer, and
+// the input gradient through the last one), one 4 x 8 x 16 tile a workgroup:
+// one K = 32 step packs the 8 channels of 4 stencil offsets, lane group g
+// taking offset 4s + g, so the weights of a wave's output block (7 steps) stay
+// in registers.  Two waves share a plane, one per output block, and go through
+// it row by row: 70 registers a wave, so twelve and more waves per CU hide the
+// tile's loads and the epilogue, which bounds this kernel (57 of 85 us for 128^3
+// with GELU; four waves a tile with both blocks and all rows at once: 103 us).
+template <int RY, int MODE>
+__global__ __launch_bounds__(512, 4) void conv8_fwd_tiled(ConvArgs a) {
     constexpr int ZR = 18, YR = RY + 2, PL = 6, KS = 7;
     __shared__ __align__(16) uint16_t tin[PL * YR * ZR * 8];
     const uint16_t* __restrict__ in = reinterpret_cast<const uint16_t*>(a.in);
     const uint16_t* __restrict__ wg = reinterpret_cast<const uint16_t*>(a.w);
     const int N = a.N;
     const int nzt = N / 16, nyt = N / RY;
-    int t = blockIdx.x;
+    int t = xcd_order(blockIdx.x, gridDim.x);
     const int tz = t % nzt;
     t /= nzt;
     const int ty = t % nyt;
     const int tx = t / nyt;
     const int x0 = tx * 4, y0 = ty * RY, z0 = tz * 16;
     constexpr int SITES = PL * YR * ZR;
-    constexpr int ITER = (SITES + 255) / 256;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    constexpr int ITER = (SITES + 511) / 512;
+    const int lane = threadIdx.x & 63, w = (threadIdx.x >> 6) & 3;
     const int n = lane & 15, g = lane >> 4;
+    const int bs = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);  // output block of this wave
     // the weights (they do not depend on the tile) and all loads of the tile
     // first, then all LDS stores (past the last site a thread re-reads it, in
     // bounds, and stores nothing)
-    bf16x8 wa[KS][2];
+    bf16x8 wa[KS];
     int off[KS];
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
         const int o = 4 * s + g;  // 27 is the all-zero padding offset
-#pragma unroll
-        for (int b = 0; b < 2; ++b) wa[s][b] = load8(wg + static_cast<size_t>(o * 32 + 16 * b + n) * 8);
+        wa[s] = load8(wg + static_cast<size_t>(o * 32 + 16 * bs + n) * 8);
         const int dx = o / 9, dy = (o / 3) % 3, dz = o % 3;
         off[s] = o < 27 ? (((w + dx) * YR + dy) * ZR + n + dz) * 8 : -1;
     }
     u32x4 v[ITER];
 #pragma unroll
     for (int k = 0; k < ITER; ++k) {
-        const int i = min(static_cast<int>(threadIdx.x) + k * 256, SITES - 1);
+        const int i = min(static_cast<int>(threadIdx.x) + k * 512, SITES - 1);
         const int zi = i % ZR, yi = (i / ZR) % YR, pi = i / (ZR * YR);
         int xx = x0 - 1 + pi, yy = y0 - 1 + yi, zz = z0 - 1 + zi;
         xx = xx < 0 ? xx + N : (xx >= N ? xx - N : xx);
@@ -429,81 +542,43 @@ __global__ __launch_bounds__(256, 2) void conv8_fwd_tiled(ConvArgs a) {
         v[k] = *reinterpret_cast<const u32x4*>(in + static_cast<size_t>((xx * N + yy) * N + zz) * 8);
     }
     // pre-activations for the input gradient's epilogue, in flight with the tile
-    const int x = x0 + w;
-    uint2 zg[RY][2];
-    if (a.gz) {
+    const int x = x0 + w, c0 = 16 * bs + 4 * g;
+    const size_t site0 = static_cast<size_t>((x * N + y0) * N + z0 + n);
+    uint2 zg[RY];
+    if constexpr (MODE == kEpiGeluGrad) {
 #pragma unroll
         for (int r = 0; r < RY; ++r)
-#pragma unroll
-            for (int b = 0; b < 2; ++b)
-                zg[r][b] = *reinterpret_cast<const uint2*>(reinterpret_cast<const uint16_t*>(a.gz) +
-                                                           static_cast<size_t>((x * N + y0 + r) * N + z0 + n) * a.gz_stride +
-                                                           16 * b + 4 * g);
+            zg[r] = *reinterpret_cast<const uint2*>(reinterpret_cast<const uint16_t*>(a.gz) + (site0 + r * N) * a.gz_stride + c0);
     }
+    float bias[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) bias[q] = a.bias ? a.bias[c0 + q] : 0.f;
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int k = 0; k < ITER; ++k) {
-        const int i = static_cast<int>(threadIdx.x) + k * 256;
+        const int i = static_cast<int>(threadIdx.x) + k * 512;
         if (i < SITES) *reinterpret_cast<u32x4*>(tin + static_cast<size_t>(i) * 8) = v[k];
     }
     __syncthreads();
-    f32x4 acc[RY][2];
+    // row by row: the stores of a row leave while the next row's products run
 #pragma unroll
-    for (int r = 0; r < RY; ++r)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) acc[r][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int r = 0; r < RY; ++r)
+    for (int r = 0; r < RY; ++r) {
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
             const bf16x8 xb = off[s] >= 0 ? load8(tin + off[s] + r * ZR * 8) : zero8();
-#pragma unroll
-            for (int b = 0; b < 2; ++b) acc[r][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa[s][b], xb, acc[r][b], 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa[s], xb, acc, 0, 0, 0);
         }
-    float bias[2][4];
+        float u[4];
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) bias[b][q] = a.bias ? a.bias[16 * b + 4 * g + q] : 0.f;
-    // every output value first, then all stores back to back
-    f32x4 zf[RY][2];
-    uint2 zh[RY][2], ao[RY][2];
-#pragma unroll
-    for (int r = 0; r < RY; ++r)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            float v[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) v[q] = acc[r][b][q] + bias[b][q];
-            zf[r][b] = f32x4{v[0], v[1], v[2], v[3]};
-            if (a.zh_out) zh[r][b] = cvt4(v);
-            if (a.a_out) {
-                float h[4];
-                if (a.gz) {
-                    float zv[4];
-                    unpack4(zg[r][b], zv);
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) h[q] = v[q] * gelu_grad(zv[q]);
-                } else if (a.gelu) {
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) h[q] = gelu(v[q]);
-                } else {
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) h[q] = v[q];
-                }
-                ao[r][b] = cvt4(h);
-            }
-        }
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int r = 0; r < RY; ++r) {
-        const size_t site = static_cast<size_t>((x * N + y0 + r) * N + z0 + n);
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            const int c0 = 16 * b + 4 * g;
-            if (a.z_out) *reinterpret_cast<f32x4*>(a.z_out + site * a.z_stride + c0) = zf[r][b];
-            if (a.zh_out) *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.zh_out) + site * a.zh_stride + c0) = zh[r][b];
-            if (a.a_out) *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.a_out) + site * a.a_stride + c0) = ao[r][b];
+        for (int q = 0; q < 4; ++q) u[q] = acc[q] + bias[q];
+        const size_t site = site0 + r * N;
+        if constexpr (MODE == kEpiZ) {
+            *reinterpret_cast<f32x4*>(a.z_out + site * a.z_stride + c0) = f32x4{u[0], u[1], u[2], u[3]};
+        } else {
+            if constexpr (MODE == kEpiGeluKeep)
+                *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.zh_out) + site * a.zh_stride + c0) = cvt4(u);
+            *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.a_out) + site * a.a_stride + c0) = epilogue4<MODE>(u, zg[r]);
         }
     }
 }
@@ -891,14 +966,35 @@ __global__ void unpack_jump(UnpackArgs a) {
 hipError_t launch_conv_fwd(const ConvArgs& a, int cin, int nb, int grid, hipStream_t s) {
     const int no = cin == 32 ? 27 : 28;
     const size_t lds = static_cast<size_t>(no) * nb * 16 * cin * 2;
-    if (cin == 32 && a.N >= 16 && a.N % 16 == 0 && a.cout <= 16 * nb) {
+    // the outputs of one of the tiled kernels' epilogues, or of none of them
+    const bool z = a.z_out && !a.zh_out && !a.a_out, act = !a.z_out && a.a_out;
+    const int mode = z                                  ? kEpiZ
+                     : act && a.gz && !a.zh_out         ? kEpiGeluGrad
+                     : act && !a.gz && a.gelu           ? (a.zh_out ? kEpiGeluKeep : kEpiGelu)
+                                                        : -1;
+    const bool tiled = a.N >= 16 && a.N % 16 == 0 && mode >= 0 && (a.cout == 32 || mode == kEpiZ);
+    if (cin == 32 && tiled && (nb == 2 ? a.cout == 32 : mode == kEpiZ && a.cout <= 16)) {
+        // one column of 8 x 16 output sites per workgroup, its march in as many
+        // pieces as fill the chip once: a workgroup has a CU to itself (115 KB of
+        // LDS), and every piece pays for its weights, its first six planes and the
+        // epilogue of its last step by itself
+        constexpr int kCUs = 256;
+        const int cols = (a.N / 8) * (a.N / 16), steps = a.N / 4;
+        const int chunks = std::min(steps, std::max(1, kCUs / cols));
+        const int L = (steps + chunks - 1) / chunks;
+        auto k = nb == 1                 ? conv32_march<8, 1, kEpiZ>
+                 : mode == kEpiZ         ? conv32_march<8, 2, kEpiZ>
+                 : mode == kEpiGelu      ? conv32_march<8, 2, kEpiGelu>
+                 : mode == kEpiGeluKeep  ? conv32_march<8, 2, kEpiGeluKeep>
+                                         : conv32_march<8, 2, kEpiGeluGrad>;
+        hipLaunchKernelGGL(k, dim3(cols * ((steps + L - 1) / L)), dim3(512), 0, s, a, L);
+    } else if (cin == 8 && nb == 2 && tiled && a.cout == 32) {
         // one workgroup per 4 x 8 x 16 block of output sites
-        const int tiles = (a.N / 4) * (a.N / 8) * (a.N / 16);
-        if (nb == 2) hipLaunchKernelGGL((conv32_fwd_tiled<8, 2>), dim3(tiles), dim3(256), 0, s, a);
-        else hipLaunchKernelGGL((conv32_fwd_tiled<8, 1>), dim3(tiles), dim3(256), 0, s, a);
-    } else if (cin == 8 && nb == 2 && a.N >= 16 && a.N % 16 == 0 && a.cout == 32) {
-        const int tiles = (a.N / 4) * (a.N / 8) * (a.N / 16);
-        hipLaunchKernelGGL((conv8_fwd_tiled<8>), dim3(tiles), dim3(256), 0, s, a);
+        auto k = mode == kEpiZ          ? conv8_fwd_tiled<8, kEpiZ>
+                 : mode == kEpiGelu     ? conv8_fwd_tiled<8, kEpiGelu>
+                 : mode == kEpiGeluKeep ? conv8_fwd_tiled<8, kEpiGeluKeep>
+                                        : conv8_fwd_tiled<8, kEpiGeluGrad>;
+        hipLaunchKernelGGL(k, dim3((a.N / 4) * (a.N / 8) * (a.N / 16)), dim3(512), 0, s, a);
     } else if (cin == 32 && nb == 2) hipLaunchKernelGGL((conv_fwd<32, 2, 4>), dim3(grid), dim3(256), lds, s, a);
     else if (cin == 32 && nb == 1) hipLaunchKernelGGL((conv_fwd<32, 1, 4>), dim3(grid), dim3(256), lds, s, a);
     else if (cin == 8 && nb == 2) hipLaunchKernelGGL((conv_fwd<8, 2, 4>), dim3(grid), dim3(256), lds, s, a);

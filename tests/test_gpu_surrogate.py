@@ -75,6 +75,21 @@ def test_forward_matches_oracle(layers, extra, tolf, N):
     s.close()
 
 
+@pytest.mark.parametrize("n,N", [(32, 128), (64, 256)])
+def test_forward_of_repeated_input(n, N):
+    """The convolutions march along x with a ring of planes, which is reused
+    from the second step on (128^3: 16 steps a piece, 256^3: 64).  The input
+    of n^3 repeated to N^3 has the output of n^3 repeated: the same operands in
+    the same order, so every value is the same."""
+    lib = _lib()
+    s = lib.Surrogate(n_fields=2, extra_inputs=4, layers=3, init_seed=3)
+    x = np.random.default_rng(6).standard_normal((s.cin, n, n, n)).astype(np.float32)
+    r = N // n
+    want = np.tile(s.forward(x), (1, r, r, r))
+    assert np.array_equal(s.forward(np.tile(x, (1, r, r, r))), want)
+    s.close()
+
+
 def emulated_backward(params, x, t):
     """FP64 forward and backward with the GPU's BF16 roundings (the layer
     inputs and weights, the output gradient 2 (y - t) / n, the
