@@ -106,6 +106,10 @@ hipError_t launch_adam(float* theta, const float* grad, float* m, float* v, int 
 hipError_t launch_prepare_layer(const PrepArgs& a, hipStream_t s);
 hipError_t launch_pack_state(const PackArgs& a, bool fp32, hipStream_t s);
 hipError_t launch_pack_sample(const SampleArgs& a, hipStream_t s);
+// c (<= 8) FP32 channels [c][n3] to BF16 [n3][8], and the first c channels of
+// FP32 [n3][stride] to [c][n3].
+hipError_t launch_pack_input(const float* x, int c, size_t n3, void* out, hipStream_t s);
+hipError_t launch_channels_first(const float* in, int stride, int c, size_t n3, float* out, hipStream_t s);
 hipError_t launch_unpack_jump(const UnpackArgs& a, bool fp32, hipStream_t s);
 
 }  // namespace sg

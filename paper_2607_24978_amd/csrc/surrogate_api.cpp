@@ -333,20 +333,14 @@ bool valid_net_N(int N) { return N >= 16 && (N & (N - 1)) == 0; }
 // The weight-gradient kernel takes 32-site segments of one z row.
 bool valid_train_N(int N) { return N >= 32 && (N & (N - 1)) == 0; }
 
-// Host FP32 [c][n3] -> BF16 [site][8] in s->x0 (through a staging upload).
+// Host FP32 [c][n3] -> BF16 [site][8] in s->x0, packed on the device.  The
+// FP32 values land in s->y (8 floats a site), which holds nothing before the
+// forward pass.
 cl_status upload_input(cl_surrogate* s, int N, const float* x) {
     const size_t n3 = static_cast<size_t>(N) * N * N;
     const int c = cin0(s);
-    std::vector<uint16_t> h(n3 * 8, 0);
-    for (int k = 0; k < c; ++k)
-        for (size_t i = 0; i < n3; ++i) {
-            uint32_t u;
-            std::memcpy(&u, &x[k * n3 + i], 4);
-            u += 0x7FFFu + ((u >> 16) & 1u);
-            h[i * 8 + k] = static_cast<uint16_t>(u >> 16);
-        }
-    SHIP(hipMemcpyAsync(s->x0, h.data(), h.size() * 2, hipMemcpyHostToDevice, s->stream));
-    SHIP(hipStreamSynchronize(s->stream));
+    SHIP(hipMemcpyAsync(s->y, x, c * n3 * sizeof(float), hipMemcpyHostToDevice, s->stream));
+    SHIP(cl::sg::launch_pack_input(s->y, c, n3, s->x0, s->stream));
     return CL_OK;
 }
 
@@ -653,11 +647,11 @@ cl_status cl_surrogate_forward(cl_surrogate* s, int N, const float* x, float* y)
     if (st) return st;
     const size_t n3 = static_cast<size_t>(N) * N * N;
     const int ys = ystride(s), co = s->L.back().cout;
-    std::vector<float> h(n3 * ys);
-    SHIP(hipMemcpyAsync(h.data(), s->y, h.size() * 4, hipMemcpyDeviceToHost, s->stream));
+    // the input (16 bytes a site) has been used: room for the at most 4 output channels
+    float* out = reinterpret_cast<float*>(s->x0);
+    SHIP(cl::sg::launch_channels_first(s->y, ys, co, n3, out, s->stream));
+    SHIP(hipMemcpyAsync(y, out, co * n3 * sizeof(float), hipMemcpyDeviceToHost, s->stream));
     SHIP(hipStreamSynchronize(s->stream));
-    for (int c = 0; c < co; ++c)
-        for (size_t i = 0; i < n3; ++i) y[c * n3 + i] = h[i * ys + c];
     return CL_OK;
 }
 
@@ -671,21 +665,19 @@ cl_status cl_surrogate_loss_grad(cl_surrogate* s, int N, const float* x, const f
     if (st) return st;
     const size_t n3 = static_cast<size_t>(N) * N * N;
     const int co = s->L.back().cout;
-    SHIP(hipMemcpyAsync(s->target, t, n3 * co * sizeof(float), hipMemcpyHostToDevice, s->stream));
+    // the target is copied while the forward pass runs
     st = forward(s, N, true);
     if (st) return st;
+    SHIP(hipMemcpyAsync(s->target, t, n3 * co * sizeof(float), hipMemcpyHostToDevice, s->stream));
     st = loss_and_backward(s, N, loss, grad_x != nullptr);
     if (st) return st;
     SHIP(hipMemcpyAsync(grad, s->grad, s->nparams * sizeof(float), hipMemcpyDeviceToHost, s->stream));
-    std::vector<float> gx;
     if (grad_x) {
-        gx.resize(n3 * 32);
-        SHIP(hipMemcpyAsync(gx.data(), s->dA, gx.size() * 4, hipMemcpyDeviceToHost, s->stream));
+        // the output has been used: its 8 floats a site take the input channels
+        SHIP(cl::sg::launch_channels_first(s->dA, 32, cin0(s), n3, s->y, s->stream));
+        SHIP(hipMemcpyAsync(grad_x, s->y, cin0(s) * n3 * sizeof(float), hipMemcpyDeviceToHost, s->stream));
     }
     SHIP(hipStreamSynchronize(s->stream));
-    if (grad_x)
-        for (int c = 0; c < cin0(s); ++c)
-            for (size_t i = 0; i < n3; ++i) grad_x[c * n3 + i] = gx[i * 32 + c];
     return CL_OK;
 }
 

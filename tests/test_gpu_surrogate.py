@@ -173,6 +173,28 @@ def test_gradients_match_oracle_elementwise(N):
     s.close()
 
 
+@pytest.mark.parametrize("nf,extra", [(1, 0), (1, 3), (2, 1)])
+def test_channel_counts(nf, extra):
+    """The input is packed, and outputs and input gradients are put back into
+    channel order, on the device: networks with 2 and 4 outputs and 2, 4 and 5
+    inputs (4 and 8 are the padded counts), within the bounds of the forward
+    and gradient checks above."""
+    lib = _lib()
+    N = 32
+    s = lib.Surrogate(n_fields=nf, extra_inputs=extra, layers=2, init_seed=4)
+    params = unflatten(s.get_params(), [s.cin, 32, s.cout])
+    rng = np.random.default_rng(12)
+    x = rng.standard_normal((s.cin, N, N, N)).astype(np.float32)
+    t = rng.standard_normal((s.cout, N, N, N)).astype(np.float32)
+    ref, absacc = emulated_forward(params, x)
+    assert np.all(np.abs(s.forward(x) - ref) <= 2 ** -7 * absacc + 1e-6)
+    loss, _, gx = s.loss_grad(x, t, input_grad=True)
+    lo, _, _, dx, dx_abs = emulated_backward(params, x.astype(np.float64), t.astype(np.float64))
+    assert abs(loss - lo) <= 2e-2 * lo and gx.shape == x.shape
+    assert np.all(np.abs(gx - dx) <= 2.0 ** -6 * dx_abs)
+    s.close()
+
+
 def test_adam_matches_oracle():
     """Three Adam steps of the device kernel (FP32) on caller-supplied
     gradients against the FP64 oracle step (Kingma and Ba, bias-corrected).
