@@ -95,6 +95,15 @@ inline int pass_flags(size_t touched, int pass, int dim = 3) {
 // f_0 .. f_{nf-1}, pi_0 .. pi_{nf-1} follow each other, each N values along z:
 // element (a, x, y, z) at ((x*N + y)*2*nf + a)*N + z.  A pass then reads one
 // contiguous address stream and writes another.
+// What a sequence of passes leaves for the host: the scalars and, of calls of
+// at most kMirrorRecords records, the records.  Pinned memory that the closing
+// kernel writes, so that the host only waits for it.
+constexpr int kMirrorRecords = 256;
+struct HostMirror {
+    Scal sc;
+    cl_observables obs[kMirrorRecords];
+};
+
 struct PassArgs {
     const void* in;   // state read by the pass
     void* out;        // state written by the pass (the ping-pong partner)
@@ -136,6 +145,8 @@ struct PassArgs {
     void* aux;
     const void* y0;
     cl_observables* obs;
+    HostMirror* mirror;  // closing kernel: also leaves the scalars and obs[0 .. mirror_n) here
+    int mirror_n, pad4_;
     Phys ph;
 };
 
@@ -362,6 +373,7 @@ struct cl_lattice {
     cl::Scal* scb = nullptr;     // two scratch scalar blocks for the passes inside a call
     cl_observables* obs = nullptr;
     int obs_cap = 0;
+    cl::HostMirror* mirror = nullptr;  // pinned
     cl::Tile tile;
     int64_t step = 0;
     // background last seen on the host (after a call synchronised with the

@@ -226,11 +226,14 @@ struct PassSeq {
         ++p;
         return e;
     }
-    hipError_t close() {
+    // n: records the sequence has written
+    hipError_t close(int n) {
         if (p == 0) return hipSuccess;
         PassArgs f = prev;
         chain(f);
         f.sc_out = h->sc;
+        f.mirror = h->mirror;
+        f.mirror_n = n <= cl::kMirrorRecords ? n : 0;
         return cl::launch_finish(f, tile, h->nf, h->stream);
     }
 };
@@ -490,7 +493,7 @@ cl_status issue_rk4_classic_steps(cl_lattice* h, double dt, int n, int cur, cons
     z.kt = z.kb = z.h_next = 0.0;
     z.rec = n - 1;
     HIPCHECK(h, seq.launch(z));
-    HIPCHECK(h, seq.close());
+    HIPCHECK(h, seq.close(n));
     return CL_OK;
 }
 
@@ -526,7 +529,7 @@ cl_status issue_rk_steps(cl_lattice* h, cl_integrator integ, double dt, int n, i
     z.kt = z.kb = z.h_next = 0.0;
     z.rec = n - 1;
     HIPCHECK(h, seq.launch(z));
-    HIPCHECK(h, seq.close());
+    HIPCHECK(h, seq.close(n));
     return CL_OK;
 }
 
@@ -560,7 +563,7 @@ cl_status issue_steps(cl_lattice* h, cl_integrator integ, double dt, int n, int 
         HIPCHECK(h, seq.launch(d));
         cur ^= 1;
     }
-    HIPCHECK(h, seq.close());
+    HIPCHECK(h, seq.close(n));
     return CL_OK;
 }
 
@@ -571,7 +574,7 @@ cl_status init_scalars(cl_lattice* h, double a, double b, double eta, const doub
 }
 
 // One reduction-only pass over the current state into obs[0].
-// sc_out (nullable): the scalar block after the pass, copied before the wait
+// sc_out (nullable): the scalar block after the pass
 cl_status reduce_pass(cl_lattice* h, cl_observables* out, Scal* sc_out = nullptr) {
     cl_status st = ensure_obs(h, 1);
     if (st) return st;
@@ -585,10 +588,10 @@ cl_status reduce_pass(cl_lattice* h, cl_observables* out, Scal* sc_out = nullptr
     r.rec = 0;
     PassSeq seq(h, t);
     HIPCHECK(h, seq.launch(r));
-    HIPCHECK(h, seq.close());
-    HIPCHECK(h, hipMemcpyAsync(out, h->obs, sizeof(cl_observables), hipMemcpyDeviceToHost, h->stream));
-    if (sc_out) HIPCHECK(h, hipMemcpyAsync(sc_out, h->sc, sizeof(Scal), hipMemcpyDeviceToHost, h->stream));
+    HIPCHECK(h, seq.close(1));
     HIPCHECK(h, hipStreamSynchronize(h->stream));
+    *out = h->mirror->obs[0];
+    if (sc_out) *sc_out = h->mirror->sc;
     return CL_OK;
 }
 
@@ -782,12 +785,15 @@ cl_status finish_step(cl_lattice* h, cl_integrator integ, int n, cl_observables*
     const int stages = integ == CL_RK2 ? 2 : integ == CL_RK3 ? 3 : integ == CL_RK34 ? 4 : integ == CL_RK4 ? 5 : 0;
     const int passes = integ == CL_RK4_CLASSIC ? 0 : is_rk(integ) ? n * stages : 1 + n * substeps_per_step(integ);
     if (passes % 2) h->cur ^= 1;
-    if (per_step)
+    // the closing kernel has left the scalars in pinned memory, and the records
+    // too unless there are more than it holds
+    const bool mirrored = n <= cl::kMirrorRecords;
+    if (per_step && !mirrored)
         HIPCHECK(h, hipMemcpyAsync(per_step, w.obs, static_cast<size_t>(n) * sizeof(cl_observables),
                                    hipMemcpyDeviceToHost, h->stream));
-    Scal s;
-    HIPCHECK(h, hipMemcpyAsync(&s, h->sc, sizeof(Scal), hipMemcpyDeviceToHost, h->stream));
     HIPCHECK(h, hipStreamSynchronize(h->stream));
+    if (per_step && mirrored) std::memcpy(per_step, h->mirror->obs, static_cast<size_t>(n) * sizeof(cl_observables));
+    const Scal& s = h->mirror->sc;
     h->step += n;
     note_background(h, s.a, s.mean_f);
     if (s.nonfinite) return fail(h, CL_EUNSTABLE, "non-finite lattice sums (unstable evolution)");
@@ -877,6 +883,10 @@ cl_status cl_create_dim(int dim, int N, double dx, int n_fields, cl_precision pr
     }
     if (hipMalloc(&h->sc, sizeof(Scal)) != hipSuccess) return bail(CL_ENOMEM, "scalar block");
     if (hipMalloc(&h->scb, 2 * sizeof(Scal)) != hipSuccess) return bail(CL_ENOMEM, "scalar blocks");
+    if (hipHostMalloc(reinterpret_cast<void**>(&h->mirror), sizeof(cl::HostMirror)) != hipSuccess) {
+        h->mirror = nullptr;
+        return bail(CL_ENOMEM, "pinned records");
+    }
     if (dim == 3) {
         h->tile = start_tile(h);
     } else {
@@ -920,6 +930,7 @@ cl_status cl_destroy(cl_lattice* h) {
     if (h->partials) hipFree(h->partials);
     if (h->scb) hipFree(h->scb);
     if (h->obs) hipFree(h->obs);
+    if (h->mirror) (void)hipHostFree(h->mirror);
     if (h->own_stream && h->stream) hipStreamDestroy(h->stream);
     delete h;
     return CL_OK;
@@ -1454,7 +1465,7 @@ cl_status cl_autotune(cl_lattice* h, int reps, char* report, size_t cap) {
         PassSeq seq(h);
         if (seq.launch(a[0]) != hipSuccess || seq.launch(a[1]) != hipSuccess) {
             (void)hipGetLastError();
-            (void)seq.close();
+            (void)seq.close(0);
             return -1.0f;
         }
         hipEventRecord(e0, h->stream);
@@ -1463,7 +1474,7 @@ cl_status cl_autotune(cl_lattice* h, int reps, char* report, size_t cap) {
             (void)seq.launch(a[1]);
         }
         hipEventRecord(e1, h->stream);
-        if (seq.close() != hipSuccess || hipEventSynchronize(e1) != hipSuccess) return -1.0f;
+        if (seq.close(0) != hipSuccess || hipEventSynchronize(e1) != hipSuccess) return -1.0f;
         float ms = 0.0f;
         hipEventElapsedTime(&ms, e0, e1);
         return ms / (2 * np);
