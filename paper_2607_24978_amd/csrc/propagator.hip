@@ -402,9 +402,11 @@ __global__ __launch_bounds__(256) void prop_modes(PropModeArgs a) {
 // each array); out of place, since the lines of z = 0 and N / 2 are their own
 // mirror plane and are taken (with equal results) by two workgroups.  The
 // transfer matrices come from the table through the caches, one per mode.
-// 256^3, two fields: 225 us against 381 for the separate passes; what is left
-// is VALU issue (about 90 us) and memory (about 100) that hardly overlap with
-// two workgroups per CU, and the table (40; its next matrix is prefetched).
+// 256^3, two fields: 197 us against 381 for the separate passes; what is left
+// is VALU issue (about 70 us) and memory (about 100) that hardly overlap with
+// two workgroups per CU, the table (its next matrix is prefetched), and the
+// last 9 of the 2057 workgroups, which follow four full rounds of 512 by
+// themselves (27 us; the lines of z = 0 do not fit into the others' lanes).
 template <int NF, int N, int L>
 __global__ __launch_bounds__(L * RegPlan<N>::R2, 2) void prop_x_modes(PropModeArgs a) {
     using P = RegPlan<N>;
@@ -413,11 +415,16 @@ __global__ __launch_bounds__(L * RegPlan<N>::R2, 2) void prop_x_modes(PropModeAr
     __shared__ uint2 tri[hN + 1];  // i (i + 1) / 2 and i (i + 1) (i + 2) / 6
     const int l = threadIdx.x % L, t = threadIdx.x / L, tb = (P::R2 - t) & (P::R2 - 1);
     // Neighbouring groups of z on one XCD: A's lines straddle two groups'
-    // 128-byte segments (B's do not), which its L2 then moves once.
+    // 128-byte segments (B's do not), which its L2 then moves once.  The rows y
+    // and N - y follow each other (0, -1, 1, -2, 2, ...): they use the same
+    // matrices, 0.5 MB a row for N = 256, which the L2 then reads once for both
+    // (256^3, two fields: 197 us, rows in order of y 221).
     constexpr int nzb = hN / L;
     const int b = xcd_order(blockIdx.x, gridDim.x);
     const bool column = b >= N * nzb;  // the last hN / L + 1 workgroups: z = 0, 16 consecutive y
-    const int y = column ? (b - N * nzb) * L + l : b / nzb, z = column ? 0 : (b % nzb) * L + l + 1;
+    const int row = b / nzb;
+    const int y = column ? (b - N * nzb) * L + l : row & 1 ? N - (row + 1) / 2 : row / 2;
+    const int z = column ? 0 : (b % nzb) * L + l + 1;
     const int yb = (N - y) & (N - 1), zb = (N - z) & (N - 1);
     // 32-bit byte offsets from the (uniform) array bases; formed again for the
     // stores, so that no address stays in registers in between
