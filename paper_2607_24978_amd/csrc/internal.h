@@ -88,13 +88,6 @@ inline int pass_flags(size_t touched, int pass, int dim = 3) {
     return (touched > (dim == 3 ? 2 : 1) * kMallBytes ? kPassNtStore : 0) | (pass & 1 ? kPassReverse : 0);
 }
 
-// One pass over the lattice: optional drift, kick, lattice sums and the
-// last-workgroup background update.
-//
-// Device layout of a state buffer: for every (x, y) row, the 2*nf arrays
-// f_0 .. f_{nf-1}, pi_0 .. pi_{nf-1} follow each other, each N values along z:
-// element (a, x, y, z) at ((x*N + y)*2*nf + a)*N + z.  A pass then reads one
-// contiguous address stream and writes another.
 // What a sequence of passes leaves for the host: the scalars and, of calls of
 // at most kMirrorRecords records, the records.  Pinned memory that the closing
 // kernel writes, so that the host only waits for it.
@@ -104,6 +97,13 @@ struct HostMirror {
     cl_observables obs[kMirrorRecords];
 };
 
+// One pass over the lattice: optional drift, kick, lattice sums and the
+// last-workgroup background update.
+//
+// Device layout of a state buffer: for every (x, y) row, the 2*nf arrays
+// f_0 .. f_{nf-1}, pi_0 .. pi_{nf-1} follow each other, each N values along z:
+// element (a, x, y, z) at ((x*N + y)*2*nf + a)*N + z.  A pass then reads one
+// contiguous address stream and writes another.
 struct PassArgs {
     const void* in;   // state read by the pass
     void* out;        // state written by the pass (the ping-pong partner)

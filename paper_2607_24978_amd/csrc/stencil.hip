@@ -1164,8 +1164,7 @@ __global__ __launch_bounds__(256, NF == 2 ? 1 : MAXRY == 2 ? 2 : 3) void ensembl
         __syncthreads();
         const int it = item_s;
         if (it >= E.nitems) break;
-        // (odd passes also take the items in the opposite order)
-        const EnsItem I = E.items[E.flags & kPassReverse ? E.nitems - 1 - it : it];
+        const EnsItem I = E.items[it];
         const EnsMember& M = E.members[I.member];
         const double kt = E.ckt * M.dt, kb = E.ckb * M.dt;
         TileJob J;
