@@ -62,8 +62,6 @@ struct cl_surrogate {
     float *theta = nullptr, *grad = nullptr, *m = nullptr, *v = nullptr;
     int adam_t = 0;
     hipStream_t stream = nullptr;
-    hipStream_t copy = nullptr;           // carries the target of loss_grad beside the forward pass
-    hipEvent_t target_free = nullptr, target_there = nullptr;
     // activation buffers for one lattice size
     int bufN = 0;
     uint16_t* x0 = nullptr;               // [n3][8]
@@ -563,11 +561,7 @@ cl_status cl_surrogate_create(const cl_surrogate_cfg* cfg, cl_surrogate** out) {
         cl_surrogate_destroy(s);
         return sfail(st, m);
     };
-    if (hipStreamCreateWithFlags(&s->stream, hipStreamNonBlocking) != hipSuccess ||
-        hipStreamCreateWithFlags(&s->copy, hipStreamNonBlocking) != hipSuccess)
-        return bail(CL_EDEVICE, "stream");
-    for (hipEvent_t* e : {&s->target_free, &s->target_there})
-        if (hipEventCreateWithFlags(e, hipEventDisableTiming) != hipSuccess) return bail(CL_EDEVICE, "event");
+    if (hipStreamCreateWithFlags(&s->stream, hipStreamNonBlocking) != hipSuccess) return bail(CL_EDEVICE, "stream");
     s->theta = dalloc<float>(off);
     s->grad = dalloc<float>(off);
     s->m = dalloc<float>(off);
@@ -610,11 +604,7 @@ cl_status cl_surrogate_destroy(cl_surrogate* s) {
         if (p) hipFree(p);
     if (s->psteps_host) hipHostFree(s->psteps_host);
     if (s->jump_obs) hipHostFree(s->jump_obs);
-    if (s->copy) hipStreamSynchronize(s->copy);
-    for (hipEvent_t e : {s->target_free, s->target_there})
-        if (e) hipEventDestroy(e);
-    for (hipStream_t q : {s->copy, s->stream})
-        if (q) hipStreamDestroy(q);
+    if (s->stream) hipStreamDestroy(s->stream);
     delete s;
     return CL_OK;
 }
@@ -671,19 +661,14 @@ cl_status cl_surrogate_loss_grad(cl_surrogate* s, int N, const float* x, const f
     if (!valid_train_N(N)) return sfail(CL_EINVAL, "N must be a power of two >= 32");
     cl_status st = ensure_bufs(s, N, true);
     if (st) return st;
-    const size_t n3 = static_cast<size_t>(N) * N * N;
-    const int co = s->L.back().cout;
-    SHIP(hipEventRecord(s->target_free, s->stream));  // nothing before this call reads the target any more
     st = upload_input(s, N, x);
     if (st) return st;
+    const size_t n3 = static_cast<size_t>(N) * N * N;
+    const int co = s->L.back().cout;
+    // the target is copied while the forward pass runs
     st = forward(s, N, true);
     if (st) return st;
-    // the target is copied while the forward pass runs (64^3: 116 us that the
-    // GPU had nothing to do in before)
-    SHIP(hipStreamWaitEvent(s->copy, s->target_free, 0));
-    SHIP(hipMemcpyAsync(s->target, t, n3 * co * sizeof(float), hipMemcpyHostToDevice, s->copy));
-    SHIP(hipEventRecord(s->target_there, s->copy));
-    SHIP(hipStreamWaitEvent(s->stream, s->target_there, 0));
+    SHIP(hipMemcpyAsync(s->target, t, n3 * co * sizeof(float), hipMemcpyHostToDevice, s->stream));
     st = loss_and_backward(s, N, loss, grad_x != nullptr);
     if (st) return st;
     SHIP(hipMemcpyAsync(grad, s->grad, s->nparams * sizeof(float), hipMemcpyDeviceToHost, s->stream));
