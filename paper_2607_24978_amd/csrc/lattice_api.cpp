@@ -17,6 +17,8 @@
 #include <cstdlib>
 #include <algorithm>
 #include <array>
+#include <functional>
+#include <mutex>
 #include <cstring>
 #include <new>
 #include <string>
@@ -122,6 +124,56 @@ cl_status ensure_partials(cl_lattice* h, int nblocks = 0) {
     h->partials_cap = need;
     drop_graph(h);
     return CL_OK;
+}
+
+// Pinned blocks for the handles, eight from one allocation (a pinned allocation
+// of its own, 60 us, would be a tenth of cl_create).  Shared by all threads; an
+// allocation goes back when its last block does.
+struct MirrorSlab {
+    cl::HostMirror* base;
+    unsigned used;  // bit per block
+};
+constexpr int kSlabBlocks = 8;
+std::mutex g_slab_mu;
+std::vector<MirrorSlab>& slabs() {
+    static std::vector<MirrorSlab>& blocks = *new std::vector<MirrorSlab>;  // outlives handles destroyed at exit
+    return blocks;
+}
+
+cl::HostMirror* take_mirror() {
+    std::lock_guard<std::mutex> lock(g_slab_mu);
+    std::vector<MirrorSlab>& all = slabs();
+    for (MirrorSlab& b : all)
+        for (int i = 0; i < kSlabBlocks; ++i)
+            if (!(b.used >> i & 1)) {
+                b.used |= 1u << i;
+                return b.base + i;
+            }
+    void* p = nullptr;
+    // portable: handles of every device take blocks from it
+    if (hipHostMalloc(&p, kSlabBlocks * sizeof(cl::HostMirror), hipHostMallocPortable) != hipSuccess) return nullptr;
+    try {
+        all.push_back({static_cast<cl::HostMirror*>(p), 1u});
+    } catch (const std::bad_alloc&) {
+        (void)hipHostFree(p);
+        return nullptr;
+    }
+    return all.back().base;
+}
+
+void give_mirror(cl::HostMirror* m) {
+    std::lock_guard<std::mutex> lock(g_slab_mu);
+    std::vector<MirrorSlab>& all = slabs();
+    for (size_t k = 0; k < all.size(); ++k) {
+        MirrorSlab& b = all[k];
+        if (std::less<cl::HostMirror*>()(m, b.base) || !std::less<cl::HostMirror*>()(m, b.base + kSlabBlocks)) continue;
+        b.used &= ~(1u << (m - b.base));
+        if (!b.used) {
+            (void)hipHostFree(b.base);
+            all.erase(all.begin() + k);
+        }
+        return;
+    }
 }
 
 cl_status ensure_obs(cl_lattice* h, int n) {
@@ -883,10 +935,8 @@ cl_status cl_create_dim(int dim, int N, double dx, int n_fields, cl_precision pr
     }
     if (hipMalloc(&h->sc, sizeof(Scal)) != hipSuccess) return bail(CL_ENOMEM, "scalar block");
     if (hipMalloc(&h->scb, 2 * sizeof(Scal)) != hipSuccess) return bail(CL_ENOMEM, "scalar blocks");
-    if (hipHostMalloc(reinterpret_cast<void**>(&h->mirror), sizeof(cl::HostMirror)) != hipSuccess) {
-        h->mirror = nullptr;
-        return bail(CL_ENOMEM, "pinned records");
-    }
+    h->mirror = take_mirror();
+    if (!h->mirror) return bail(CL_ENOMEM, "pinned records");
     if (dim == 3) {
         h->tile = start_tile(h);
     } else {
@@ -930,7 +980,7 @@ cl_status cl_destroy(cl_lattice* h) {
     if (h->partials) hipFree(h->partials);
     if (h->scb) hipFree(h->scb);
     if (h->obs) hipFree(h->obs);
-    if (h->mirror) (void)hipHostFree(h->mirror);
+    if (h->mirror) give_mirror(h->mirror);
     if (h->own_stream && h->stream) hipStreamDestroy(h->stream);
     delete h;
     return CL_OK;

@@ -665,7 +665,7 @@ cl_status cl_surrogate_loss_grad(cl_surrogate* s, int N, const float* x, const f
     if (st) return st;
     const size_t n3 = static_cast<size_t>(N) * N * N;
     const int co = s->L.back().cout;
-    // the target is copied while the forward pass runs
+    // the host stages the target while the forward pass runs
     st = forward(s, N, true);
     if (st) return st;
     SHIP(hipMemcpyAsync(s->target, t, n3 * co * sizeof(float), hipMemcpyHostToDevice, s->stream));
