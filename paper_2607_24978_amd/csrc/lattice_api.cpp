@@ -98,23 +98,16 @@ bool valid_N(int N, cl_precision prec) {
     return pow2 || (N % big == 0);
 }
 
-// Tile of a pass that only reduces.  It stores nothing, so twice the
-// workgroups at half the march hide more of its loads: 256^3 two fields FP32
-// 61 us against 78, 512^3 373 against 420 (with at most kTunedPassBlocks of
-// them, and marches of 16 planes or more, whose first loads stay cheap).
+// Tile of a pass that only reduces the state of h.
 Tile reduce_tile(const cl_lattice* h) {
-    Tile t = h->tile;
-    if (h->dim == 3 && !h->ng && t.CX >= 32 && t.CX % 2 == 0 && 2 * t.nblocks() <= cl::kTunedPassBlocks) {
-        t.CX /= 2;
-        cl::finalize_tile(t, h->N, h->prec);
-    }
-    return t;
+    return h->dim == 3 && !h->ng ? cl::reduction_tile(h->tile, h->N, h->prec) : h->tile;
 }
 
-// Two halves of nsums * nblocks doubles: consecutive passes alternate, as a
-// pass reads the sums of the one before while writing its own.
+// Two halves of nsums doubles per workgroup, for the passes of the handle's
+// tile, its reductions and passes of `nblocks` workgroups: consecutive passes
+// alternate, as a pass reads the sums of the one before while writing its own.
 cl_status ensure_partials(cl_lattice* h, int nblocks = 0) {
-    if (nblocks <= 0) nblocks = std::max(h->tile.nblocks(), reduce_tile(h).nblocks());
+    nblocks = std::max({nblocks, h->tile.nblocks(), reduce_tile(h).nblocks()});
     const size_t need = 2 * static_cast<size_t>(cl::nsums(h->nf)) * nblocks;
     if (need <= h->partials_cap) return CL_OK;
     if (h->partials) hipFree(h->partials);
@@ -261,6 +254,8 @@ struct PassSeq {
         a.prkdeta = prev.rkdeta;
     }
     hipError_t launch(PassArgs a) {
+        // every workgroup leaves its sums: refuse a tile that the scratch has no room for
+        if (static_cast<size_t>(cl::nsums(h->nf)) * tile.nblocks() > w.half) return hipErrorInvalidValue;
         a.partials = part(p & 1);
         a.obs = w.obs;
         // buffers a pass reads or writes: the two states, and a Runge-Kutta
@@ -1573,6 +1568,11 @@ cl_status cl_autotune(cl_lattice* h, int reps, char* report, size_t cap) {
     HIPCHECK(h, hipStreamSynchronize(h->stream));
     if (best < 0) return fail(h, CL_EDEVICE, "no candidate tile launched");
     h->tile = cands[best];
+    st = ensure_partials(h);  // its reductions may take more workgroups than any candidate
+    if (st) {
+        h->tile = keep;
+        return st;
+    }
     drop_graph(h);
     char tail[200];
     std::snprintf(tail, sizeof tail, "],\"best\":{\"tz\":%d,\"ty\":%d,\"cx\":%d,\"ry\":%d,\"pd\":%d,\"us\":%.2f}}",

@@ -1,0 +1,68 @@
+"""The rules that choose a pass's tile, called in the built library on the CPU
+(they take sizes only): every lattice size that cl_create accepts."""
+import ctypes as C
+
+import pytest
+
+PREC = {"fp64": 0, "fp32": 1}
+MAX_BLOCKS = 4096   # workgroups of a pass whose partial sums the next one reads
+TUNED_BLOCKS = 1024
+
+
+class Tile(C.Structure):
+    _fields_ = [(k, C.c_int) for k in ("TZ", "TY", "CX", "RY", "NT", "HI", "PD", "nbz", "nby", "nbx")]
+
+    @property
+    def nblocks(self):
+        return self.nbz * self.nby * self.nbx
+
+    def fits(self, N):
+        return (self.nbz * self.TZ == N and self.nby * self.TY == N and self.nbx * self.CX == N
+                and self.NT <= 512 and self.nblocks <= MAX_BLOCKS)
+
+    def __str__(self):
+        return str([getattr(self, k) for k, _ in self._fields_])
+
+
+def rule(name, restype, *argtypes):
+    from paper_2607_24978_amd import _lib
+    f = getattr(C.CDLL(_lib.LIB_PATH), name)
+    f.restype, f.argtypes = restype, argtypes
+    return f
+
+
+def default_tile(N, prec, nf):
+    return rule("_ZN2cl12default_tileEi12cl_precisioni", Tile, C.c_int, C.c_int, C.c_int)(N, PREC[prec], nf)
+
+
+def reduction_tile(t, N, prec, *nf):
+    f = rule("_ZN2cl14reduction_tileERKNS_4TileEi12cl_precision" + "i" * len(nf), Tile, C.POINTER(Tile), C.c_int, C.c_int,
+             *[C.c_int] * len(nf))
+    return f(C.byref(t), N, PREC[prec], *nf)
+
+
+def candidates(N, prec, nf):
+    f = rule("_ZN2cl15candidate_tilesEi12cl_precisioniPNS_4TileEPii", None, C.c_int, C.c_int, C.c_int, C.POINTER(Tile),
+             C.POINTER(C.c_int), C.c_int)
+    out, n = (Tile * 1024)(), C.c_int()
+    f(N, PREC[prec], nf, out, C.byref(n), len(out))
+    return list(out[:n.value])
+
+
+def sizes(prec):
+    big = 256 if prec == "fp32" else 128
+    return [N for N in range(8, 1601, 2) if N & (N - 1) == 0 or N % big == 0]
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("nf", [1, 2])
+def test_reductions_fit(prec, nf):
+    """The reductions of a lattice in its default tile or in any tile the
+    autotuner may pick are valid tiles, with more workgroups than the tile
+    itself only up to TUNED_BLOCKS."""
+    for N in sizes(prec):
+        for t in [default_tile(N, prec, nf)] + candidates(N, prec, nf):
+            assert t.fits(N), (N, str(t))
+            r = reduction_tile(t, N, prec)
+            assert r.fits(N) and r.NT == t.NT, (N, str(t), str(r))
+            assert r.nblocks <= max(t.nblocks, TUNED_BLOCKS), (N, str(t), str(r))
