@@ -294,7 +294,7 @@ int march_length(int N, int tiles, int per_round);
 // Default tile for a lattice; valid for every N accepted by cl_create.
 Tile default_tile(int N, cl_precision prec, int nf);
 // Tile of a pass that only reduces, on a lattice whose passes run in tile t.
-Tile reduction_tile(const Tile& t, int N, cl_precision prec);
+Tile reduction_tile(const Tile& t, int N, cl_precision prec, int nf);
 // Fill nbz/nby/nbx and check that the tile divides the lattice and fits the
 // kernel's limits.  Returns false if not.
 bool finalize_tile(Tile& t, int N, cl_precision prec);

@@ -100,7 +100,7 @@ bool valid_N(int N, cl_precision prec) {
 
 // Tile of a pass that only reduces the state of h.
 Tile reduce_tile(const cl_lattice* h) {
-    return h->dim == 3 && !h->ng ? cl::reduction_tile(h->tile, h->N, h->prec) : h->tile;
+    return h->dim == 3 && !h->ng ? cl::reduction_tile(h->tile, h->N, h->prec, h->nf) : h->tile;
 }
 
 // Two halves of nsums doubles per workgroup, for the passes of the handle's

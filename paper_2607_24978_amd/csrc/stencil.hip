@@ -1126,16 +1126,22 @@ Tile default_tile(int N, cl_precision prec, int nf) {
     return t;
 }
 
-// A reduction stores nothing, so twice the workgroups at half the march hide
-// more of its loads: 256^3 two fields FP32 61 us against 78, 512^3 373 against
-// 420 (with at most kTunedPassBlocks of them, and marches of 16 planes or
-// more, whose first loads stay cheap).
-Tile reduction_tile(const Tile& t, int N, cl_precision prec) {
+// A reduction stores nothing, so where a tile gives every CU at most one
+// workgroup, two at half the march hide more of its loads (marches of 16 planes
+// or more, whose first loads stay cheap): two reductions and their waits at
+// 256^3, two fields, FP32, 132 us against 184, 512^3 one field 400 against 473.
+// From 400 workgroups on the tile's own march is the better one (384^3 FP64 one
+// field 352 against 373), and eight waves of two fields fill a CU's registers,
+// so that every further workgroup starts cold (256^3 FP64 233 against 253,
+// 512^3 FP32 799 / 826).  Of eight waves of one field two workgroups run at
+// once at depth 1: 384^3 FP64 352 against 425 at depth 2, 512^3 FP32 400 / 450,
+// 640^3 FP64 1608 / 1908, 768^3 FP32 1348 / 1586.
+Tile reduction_tile(const Tile& t, int N, cl_precision prec, int nf) {
+    constexpr int kCUs = 256;
     Tile r = t;
-    if (t.CX >= 32 && t.CX % 2 == 0 && 2 * t.nblocks() <= kTunedPassBlocks) {
-        r.CX /= 2;
-        finalize_tile(r, N, prec);
-    }
+    if (t.CX >= 32 && t.CX % 2 == 0 && t.nblocks() <= kCUs && !(nf == 2 && t.NT > 256)) r.CX /= 2;
+    finalize_tile(r, N, prec);
+    if (nf == 1 && r.NT > 256 && r.nblocks() > kCUs) r.PD = 1;
     return r;
 }
 

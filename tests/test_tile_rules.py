@@ -35,10 +35,9 @@ def default_tile(N, prec, nf):
     return rule("_ZN2cl12default_tileEi12cl_precisioni", Tile, C.c_int, C.c_int, C.c_int)(N, PREC[prec], nf)
 
 
-def reduction_tile(t, N, prec, *nf):
-    f = rule("_ZN2cl14reduction_tileERKNS_4TileEi12cl_precision" + "i" * len(nf), Tile, C.POINTER(Tile), C.c_int, C.c_int,
-             *[C.c_int] * len(nf))
-    return f(C.byref(t), N, PREC[prec], *nf)
+def reduction_tile(t, N, prec, nf):
+    f = rule("_ZN2cl14reduction_tileERKNS_4TileEi12cl_precisioni", Tile, C.POINTER(Tile), C.c_int, C.c_int, C.c_int)
+    return f(C.byref(t), N, PREC[prec], nf)
 
 
 def candidates(N, prec, nf):
@@ -58,11 +57,31 @@ def sizes(prec):
 @pytest.mark.parametrize("nf", [1, 2])
 def test_reductions_fit(prec, nf):
     """The reductions of a lattice in its default tile or in any tile the
-    autotuner may pick are valid tiles, with more workgroups than the tile
-    itself only up to TUNED_BLOCKS."""
+    autotuner may pick are valid tiles of at most TUNED_BLOCKS workgroups, or
+    of as many as the tile itself."""
     for N in sizes(prec):
         for t in [default_tile(N, prec, nf)] + candidates(N, prec, nf):
             assert t.fits(N), (N, str(t))
-            r = reduction_tile(t, N, prec)
+            r = reduction_tile(t, N, prec, nf)
             assert r.fits(N) and r.NT == t.NT, (N, str(t), str(r))
             assert r.nblocks <= max(t.nblocks, TUNED_BLOCKS), (N, str(t), str(r))
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("nf", [1, 2])
+def test_reduction_march_and_depth(prec, nf):
+    """A reduction keeps the march of a tile with more workgroups than CUs, and
+    of two fields in eight-wave workgroups; of one field, eight-wave workgroups
+    that are more than the CUs run at depth 1."""
+    seen = set()
+    for N in sizes(prec):
+        for t in [default_tile(N, prec, nf)] + candidates(N, prec, nf):
+            r = reduction_tile(t, N, prec, nf)
+            wide = t.NT > 256
+            if t.nblocks > 256 or (wide and nf == 2):
+                assert r.CX == t.CX, (N, str(t))
+                seen.add("march")
+            if wide and nf == 1 and r.nblocks > 256:
+                assert r.PD == 1, (N, str(t))
+                seen.add("depth")
+    assert seen == ({"march", "depth"} if nf == 1 else {"march"})
