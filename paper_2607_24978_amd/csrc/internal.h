@@ -290,9 +290,10 @@ bool prop_modes_with_x(int N, bool fp32);
 hipError_t launch_prop_modes(const PropModeArgs& a, bool fp32, hipStream_t s);
 hipError_t launch_init_scalars(Scal* sc, double a, double b, double eta, const Phys& ph,
                                const double* shift, hipStream_t s);
-int march_length(int N, int tiles, int per_round);
 // Default tile for a lattice; valid for every N accepted by cl_create.
 Tile default_tile(int N, cl_precision prec, int nf);
+// Default tile of a pass that carries the gravitational-wave tensor.
+Tile gw_tile(int N, cl_precision prec);
 // Tile of a pass that only reduces, on a lattice whose passes run in tile t.
 Tile reduction_tile(const Tile& t, int N, cl_precision prec, int nf);
 // Fill nbz/nby/nbx and check that the tile divides the lattice and fits the

@@ -768,29 +768,9 @@ bool cached_tile(int N, int nf, cl_precision prec, Tile& t) {
     return found;
 }
 
-// Tile of a pass that carries the gravitational-wave tensor: one row per
-// thread, 16 threads along z, 128-thread workgroups (seven stencil arrays of
-// registers per thread; 40 KB of LDS in FP32), prefetch depth 1, and x-chunks
-// for rounds of 512 workgroups (one wave per SIMD, two workgroups per CU):
-// 68 us per pass at 128^3 (two fields, FP32) against 84 with 1024 shorter ones.
-Tile gw_tile(int N, cl_precision prec) {
-    const int V = prec == CL_FP32 ? 4 : 2;
-    Tile t;
-    t.TZ = std::min(N, 16 * V);
-    const int BZ = t.TZ / V;
-    int TY = 128 / BZ;
-    while (TY > 1 && (TY > N || N % TY)) TY >>= 1;
-    t.TY = TY;
-    t.RY = 1;
-    t.PD = 1;
-    t.CX = cl::march_length(N, (N / t.TZ) * (N / t.TY), 512);
-    cl::finalize_tile(t, N, prec);
-    return t;
-}
-
 // The tile a lattice starts from: the tuned cache entry or the default.
 Tile start_tile(const cl_lattice* h) {
-    if (h->ng) return gw_tile(h->N, h->prec);
+    if (h->ng) return cl::gw_tile(h->N, h->prec);
     Tile t = cl::default_tile(h->N, h->prec, h->nf);
     cached_tile(h->N, h->nf, h->prec, t);
     return t;

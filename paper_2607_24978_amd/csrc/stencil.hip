@@ -1081,7 +1081,7 @@ bool finalize_tile(Tile& t, int N, cl_precision prec) {
 // schedule, counted in plane times -- rounds of workgroups over the CUs
 // (`per_round` run at a time), each paying its planes and about eight more
 // for its start (loads in flight, the scalar step) and its end (the sums).
-int march_length(int N, int tiles, int per_round) {
+static int march_length(int N, int tiles, int per_round) {
     int best = N;
     long best_cost = -1;
     for (int cx = N; cx >= 1; --cx) {
@@ -1122,6 +1122,37 @@ Tile default_tile(int N, cl_precision prec, int nf) {
     t.TY = TY;
     t.CX = march_length(N, (N / t.TZ) * (N / t.TY), 256);
     t.PD = t.CX >= 32 ? 2 : 1;
+    finalize_tile(t, N, prec);
+    return t;
+}
+
+// Tile of a pass that carries the gravitational-wave tensor: one row per
+// thread, 16 threads along z, 128-thread workgroups (seven stencil arrays of
+// registers per thread; 40 KB of LDS in FP32), prefetch depth 1.  One wave per
+// SIMD, so two workgroups per CU run at a time; where a march through the whole
+// lattice leaves them idle, its length is that of the cheapest rounds of 512
+// (two fields FP32, two leapfrog steps of 128^3 180 us against 220 with 1024
+// workgroups of half the march, 256^3 one field 958 / 1020).  Otherwise the
+// marches are halved up to 1024 workgroups, whose uneven ends overlap: 384^3
+// FP64, two steps, 7.9 ms with 1152 workgroups against 9.6 with 576, 512^3 FP32
+// one reduction after another 2.71 ms with 1024 against 2.84 with 512.
+Tile gw_tile(int N, cl_precision prec) {
+    constexpr int kAtOnce = 512;
+    const int V = prec == CL_FP32 ? 4 : 2;
+    Tile t;
+    t.TZ = N < 16 * V ? N : 16 * V;
+    int TY = 128 / (t.TZ / V);
+    while (TY > 1 && (TY > N || N % TY)) TY >>= 1;
+    t.TY = TY;
+    t.RY = 1;
+    t.PD = 1;
+    const int tiles = (N / t.TZ) * (N / t.TY);
+    if (tiles < kAtOnce) {
+        t.CX = march_length(N, tiles, kAtOnce);
+    } else {
+        t.CX = N;
+        while (t.CX > 4 && t.CX % 2 == 0 && tiles * (N / t.CX) < 2 * kAtOnce) t.CX /= 2;
+    }
     finalize_tile(t, N, prec);
     return t;
 }

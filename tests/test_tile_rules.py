@@ -85,3 +85,18 @@ def test_reduction_march_and_depth(prec, nf):
                 assert r.PD == 1, (N, str(t))
                 seen.add("depth")
     assert seen == ({"march", "depth"} if nf == 1 else {"march"})
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_waves_tile(prec):
+    """The tile with the gravitational-wave tensor is valid at every size (those
+    whose state fits the memory: at most 1024), and where its columns alone
+    occupy the chip the marches still make at least two rounds of workgroups."""
+    f = rule("_ZN2cl7gw_tileEi12cl_precision", Tile, C.c_int, C.c_int)
+    for N in sizes(prec):
+        if N > 1024:
+            continue
+        t = f(N, PREC[prec])
+        assert t.fits(N) and t.NT <= 256 and (t.RY, t.PD) == (1, 1), (N, str(t))
+        if t.nbz * t.nby >= 512:
+            assert t.nblocks >= 1024, (N, str(t))
