@@ -398,14 +398,16 @@ __device__ __forceinline__ void static_for(F&& f) {
 // u_11.. .  They drift with the fields' coefficient and are kicked by
 // kL (L[v] + (1/m_p^2) S) where S is the traceless part of the sum over
 // fields of the products of forward and of backward differences of the
-// drifted fields (no lattice sums for them).
+// drifted fields (no lattice sums for them).  NG = -5: the state holds them,
+// but the pass only reduces and leaves them in memory.
 template <typename T, int NF, int RY, int HI, int PD, int RK, int HPD, int NG, typename Prelude>
 __device__ __forceinline__ void march_tile(const TileJob& J, unsigned char* smem_raw, double (&acc)[kSumsPerField * NF + 1],
                            Prelude&& prelude) {
     constexpr int V = VecOf<T>::V;
     constexpr int NS = kSumsPerField * NF + 1;
-    constexpr int NA = NF + NG;  // stencil arrays (fields and tensor components)
-    static_assert(NG == 0 || (NG == 5 && RK == 0), "tensor components with the symplectic schemes only");
+    constexpr int NA = NF + (NG > 0 ? NG : 0);  // stencil arrays (fields and tensor components)
+    constexpr int NR = NF + (NG > 0 ? NG : -NG);  // arrays of f (of pi) in a row of the state
+    static_assert(NG == 0 || ((NG == 5 || NG == -5) && RK == 0), "tensor components with the symplectic schemes only");
     const int N = J.N, TZ = J.TZ, TY = J.TY, CX = J.CX;
     const int z0 = J.z0, y0 = J.y0, x0 = J.x0;
     const int BZ = TZ / V;
@@ -414,8 +416,8 @@ __device__ __forceinline__ void march_tile(const TileJob& J, unsigned char* smem
     const int tid = threadIdx.x;
     const int tz = tid % BZ;
     const int tr = tid / BZ;
-    // Row-interleaved state: array a of row (x, y) starts at ((x*N + y)*2NA + a)*N.
-    const int rs = 2 * NA * N;  // row stride (elements)
+    // Row-interleaved state: array a of row (x, y) starts at ((x*N + y)*2NR + a)*N.
+    const int rs = 2 * NR * N;  // row stride (elements)
     const T* fin[NA];
     const T* pin[NA];
     T* fout[NA];
@@ -423,9 +425,9 @@ __device__ __forceinline__ void march_tile(const TileJob& J, unsigned char* smem
 #pragma unroll
     for (int j = 0; j < NA; ++j) {
         fin[j] = static_cast<const T*>(J.in) + j * N;
-        pin[j] = static_cast<const T*>(J.in) + (NA + j) * N;
+        pin[j] = static_cast<const T*>(J.in) + (NR + j) * N;
         fout[j] = static_cast<T*>(J.out) + j * N;
-        pout[j] = static_cast<T*>(J.out) + (NA + j) * N;
+        pout[j] = static_cast<T*>(J.out) + (NR + j) * N;
     }
     const bool nt_store = J.flags & kPassNtStore;
     const bool rev = J.flags & kPassReverse;
@@ -1421,6 +1423,17 @@ static hipError_t launch_nf(const PassArgs& a, const Tile& t, hipStream_t s, siz
         // with the gravitational-wave tensor: one row per thread, depth 1,
         // at most 256 threads (seven stencil arrays of registers per thread)
         if (a.ng != 5 || a.rk || t.RY != 1 || t.PD != 1 || t.NT > 256) return hipErrorInvalidValue;
+        // The sums are the fields' alone: a pass that only reduces does not
+        // load the tensor (512^3, two fields, FP32, two reductions and their
+        // waits 3.20 ms with it, 3.38 once the march could go both ways, 0.91
+        // without).
+        if (!a.write_out) {
+            if (t.HI == 1)
+                hipLaunchKernelGGL((lattice_pass<T, NF, 1, 1, 1, 0, 256, -5>), dim3(t.nblocks()), dim3(t.NT), lds, s, a);
+            else
+                hipLaunchKernelGGL((lattice_pass<T, NF, 1, 2, 1, 0, 256, -5>), dim3(t.nblocks()), dim3(t.NT), lds, s, a);
+            return hipGetLastError();
+        }
         if (t.HI == 1)
             hipLaunchKernelGGL((lattice_pass<T, NF, 1, 1, 1, 0, 256, 5>), dim3(t.nblocks()), dim3(t.NT), lds, s, a);
         else
@@ -1789,7 +1802,7 @@ hipError_t launch_pass(const PassArgs& a, const Tile& t, cl_precision prec, hipS
             return a.ph.nf == 1 ? launch_lowdim<float, 1>(a, t.nblocks(), s) : launch_lowdim<float, 2>(a, t.nblocks(), s);
         return a.ph.nf == 1 ? launch_lowdim<double, 1>(a, t.nblocks(), s) : launch_lowdim<double, 2>(a, t.nblocks(), s);
     }
-    const size_t lds = pass_lds_bytes(t, prec, a.ph.nf + a.ng);
+    const size_t lds = pass_lds_bytes(t, prec, a.ph.nf + (a.write_out ? a.ng : 0));
     if (prec == CL_FP32)
         return a.ph.nf == 1 ? launch_nf<float, 1>(a, t, s, lds) : launch_nf<float, 2>(a, t, s, lds);
     return a.ph.nf == 1 ? launch_nf<double, 1>(a, t, s, lds) : launch_nf<double, 2>(a, t, s, lds);

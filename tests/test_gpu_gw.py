@@ -214,3 +214,29 @@ def test_gw_enable_keeps_state_and_rejects_what_it_cannot_run():
         lat.gw_get()
     assert e.value.status == lib.CL_ESTATE
     lat.close()
+
+
+@pytest.mark.parametrize("N,nf,precision", [(8, 1, "fp64"), (16, 2, "fp32"), (32, 1, "fp32"), (64, 2, "fp64")])
+def test_observables_leave_the_tensor_out(N, nf, precision):
+    """A reduction of a lattice with waves does not load the tensor: it gives the
+    observables of the same fields on a lattice without, to the rounding of the
+    summation order (FP64 1e-12; FP32 lattices round each thread's plane
+    partials, 1e-6)."""
+    rng = np.random.default_rng(N)
+    f, p = 1.0 + 0.1 * rng.standard_normal((nf, N, N, N)), 0.1 * rng.standard_normal((nf, N, N, N))
+    obs = []
+    for waves in (False, True):
+        lat = _lib().Lattice(N, 0.5, nf, precision)
+        if waves:
+            lat.gw_enable()
+        lat.set_background(expansion="static")
+        lat.set_potential(lam=(1.0, 0.5), g2=2.0 if nf == 2 else 0.0)
+        lat.set_fields(f, p)
+        if waves:
+            lat.gw_set(*rng.standard_normal((2, 5, N, N, N)))
+        obs.append(lat.read_observables())
+        lat.close()
+    tol = 1e-12 if precision == "fp64" else 1e-6
+    for k in ("EK", "EG", "EV", "mean", "var"):
+        a, b = np.asarray(obs[1][k]), np.asarray(obs[0][k])
+        assert np.all(np.abs(a - b) <= tol * np.abs(b)), (k, a, b)
