@@ -1105,16 +1105,24 @@ static int march_length(int N, int tiles, int per_round) {
 // one wave (whose barriers cost nothing) while 64-thread tiles one plane
 // long number at most two per CU, two waves up to 64^3, four while the state
 // reuses the memory-side cache, and eight beyond it, where the halo rows of
-// short tiles are read from HBM again.  Measured, us per pass against the
-// former tile (256 threads, marches of at least four planes): one field 32^3
-// FP64 8.9 / 11.1, two fields 64^3 FP32 14.9 / 18.0, two fields 128^3 FP32
-// 24.2 / 30.9, two fields 256^3 FP32 99.7 / 108.9, one field 384^3 FP64
-// 344 / 382, two fields 512^3 FP32 721 / 798 (with the cache policy above).
+// short tiles are read from HBM again.  (At exactly twice the cache one field
+// takes eight and two fields four: two leapfrog steps of 256^3 FP64 one field
+// 529 us against 559 with four, of 256^3 FP32 two fields 569 against 531.)
+// Measured, us per pass against the former tile (256 threads, marches of at
+// least four planes): one field 32^3 FP64 8.9 / 11.1, two fields 64^3 FP32
+// 14.9 / 18.0, two fields 128^3 FP32 24.2 / 30.9, two fields 256^3 FP32 99.7 /
+// 108.9, one field 384^3 FP64 344 / 382, two fields 512^3 FP32 721 / 798 (with
+// the cache policy above).
+// Marches are counted in rounds of one workgroup per CU, or of two where their
+// registers allow it and there is work for them, four waves of one field:
+// 256^3 FP32 54 us a pass against 58 with marches of twice the length, its
+// Runge-Kutta stages 84 against 93 (rk4), 128^3 FP32 19.1 / 19.5.
 Tile default_tile(int N, cl_precision prec, int nf) {
     const int V = prec == CL_FP32 ? 4 : 2;
     const size_t sites = static_cast<size_t>(N) * N * N;
     const size_t touched = 4 * nf * sites * (prec == CL_FP32 ? 4 : 8);
-    const int threads = sites / V <= 32768 ? 64 : sites / V <= 131072 ? 128 : touched <= 2 * kMallBytes ? 256 : 512;
+    const bool cached = nf == 1 ? touched < 2 * kMallBytes : touched <= 2 * kMallBytes;
+    const int threads = sites / V <= 32768 ? 64 : sites / V <= 131072 ? 128 : cached ? 256 : 512;
     Tile t;
     t.TZ = N < 64 * V ? N : 64 * V;
     const int BZ = t.TZ / V;
@@ -1122,7 +1130,7 @@ Tile default_tile(int N, cl_precision prec, int nf) {
     int TY = threads / BZ;
     while (TY > 1 && (TY > N || N % TY)) TY >>= 1;
     t.TY = TY;
-    t.CX = march_length(N, (N / t.TZ) * (N / t.TY), 256);
+    t.CX = march_length(N, (N / t.TZ) * (N / t.TY), nf == 1 && threads == 256 ? 512 : 256);
     t.PD = t.CX >= 32 ? 2 : 1;
     finalize_tile(t, N, prec);
     return t;

@@ -100,3 +100,16 @@ def test_waves_tile(prec):
         assert t.fits(N) and t.NT <= 256 and (t.RY, t.PD) == (1, 1), (N, str(t))
         if t.nbz * t.nby >= 512:
             assert t.nblocks >= 1024, (N, str(t))
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_default_march_of_one_field(prec):
+    """Two four-wave workgroups of one field run on a CU: from 128^3 on their
+    march gives the chip 512 of them, as far as the lattice has columns for."""
+    seen = 0
+    for N in sizes(prec):
+        t = default_tile(N, prec, 1)
+        if N >= 128 and t.NT == 256:
+            seen += 1
+            assert t.nblocks >= 512, (N, str(t))
+    assert seen
