@@ -130,3 +130,32 @@ def test_rk_rejected_by_ensembles():
     ens.close()
     for lat in lats:
         lat.close()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("nf", [1, 2])
+@pytest.mark.parametrize("scheme", ["rk3", "rk4", "rk4_classic"])
+def test_rk_wide_workgroups(scheme, nf, precision):
+    """Eight-wave workgroups, the default of large lattices, run instances of
+    their own (low storage and classic): in static space their fields are bitwise
+    those of four-wave ones, marches of one chunk and of several, and the sums
+    agree to the rounding of their order (FP64 1e-12; FP32 lattices round each
+    thread's plane partials, 1e-6)."""
+    lib = __import__("paper_2607_24978_amd._lib", fromlist=["_lib"])
+    N = 64
+    f, p = W.random_state(N, nf, 21)
+    wide = 32 if precision == "fp32" else 16  # rows of 512 threads
+    out = []
+    for ty, cx in ((wide // 2, 16), (wide, 64), (wide, 16)):
+        lat = lib.Lattice(N, 0.5, nf, precision)
+        lat.set_tile(N, ty, cx)
+        lat.set_background(expansion="static")
+        lat.set_potential(lam=(1.0, 0.5), g2=2.0 if nf == 2 else 0.0)
+        lat.set_fields(f, p)
+        out.append((lat.step(scheme, 0.02, 3), *lat.get_fields()))
+        lat.close()
+    tol = 1e-12 if precision == "fp64" else 1e-6
+    for r, wf, wp in out[1:]:
+        assert np.array_equal(wf, out[0][1]) and np.array_equal(wp, out[0][2])
+        for k in ("EK", "EG", "EV", "var"):
+            assert np.all(np.abs(r[k] - out[0][0][k]) <= tol * np.abs(out[0][0][k])), k
