@@ -173,6 +173,32 @@ def test_gradients_match_oracle_elementwise(N):
     s.close()
 
 
+def test_gradients_of_repeated_sample():
+    """The training passes at 128^3, whose march has 16 steps a piece and so
+    reuses the ring of planes (at 64^3 it has two, at 32^3 one).  A sample of
+    32^3 repeated r = 4 times a side has the output repeated, and every
+    gradient at a site is that of 32^3 over r^3, a power of two: exactly, as
+    BF16 roundings scale with it.  Sums over the sites are equal to FP32
+    rounding: at most 2^21 / 256 terms a partial sum and 1024 of those, each
+    addition 2^-24 of the sum of absolute values."""
+    lib = _lib()
+    n, r = 32, 4
+    s = lib.Surrogate(n_fields=2, extra_inputs=4, layers=4, init_seed=5)
+    chans = [s.cin] + [32] * 3 + [s.cout]
+    rng = np.random.default_rng(15)
+    x = rng.standard_normal((s.cin, n, n, n)).astype(np.float32)
+    t = rng.standard_normal((s.cout, n, n, n)).astype(np.float32)
+    loss, g, gx = s.loss_grad(x, t, input_grad=True)
+    rep = lambda a: np.tile(a, (1, r, r, r))
+    lossN, gN, gxN = s.loss_grad(rep(x), rep(t), input_grad=True)
+    assert abs(lossN - loss) <= 1e-6 * loss
+    assert np.array_equal(gxN, rep(gx) / np.float32(r ** 3))
+    _, _, ga, _, _ = emulated_backward(unflatten(s.get_params(), chans), x.astype(np.float64), t.astype(np.float64))
+    scale = np.concatenate([np.concatenate([aW.ravel(), ab.ravel()]) for aW, ab in ga])
+    assert np.all(np.abs(gN.astype(np.float64) - g) <= (2 ** 21 / 256 + 1024) * 2.0 ** -24 * scale)
+    s.close()
+
+
 @pytest.mark.parametrize("nf,extra", [(1, 0), (1, 3), (2, 1)])
 def test_channel_counts(nf, extra):
     """The input is packed, and outputs and input gradients are put back into
