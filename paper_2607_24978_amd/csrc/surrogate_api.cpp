@@ -68,6 +68,8 @@ struct cl_surrogate {
     std::vector<uint16_t*> act;           // [layers-1] x [n3][32]
     std::vector<uint16_t*> zpre;          // [layers-1] x [n3][32] BF16 pre-activations
     float* y = nullptr;                   // [n3][4..8]
+    std::vector<uint16_t> hx;             // host copies of small lattices' input (x0) and output (y)
+    std::vector<float> hy;
     float* dA = nullptr;                  // [n3][32]
     uint16_t* dZ[2] = {nullptr, nullptr}; // [n3][32], layer gradients (ping-pong)
     uint16_t* dy = nullptr;               // [n3][8]
@@ -333,12 +335,37 @@ bool valid_net_N(int N) { return N >= 16 && (N & (N - 1)) == 0; }
 // The weight-gradient kernel takes 32-site segments of one z row.
 bool valid_train_N(int N) { return N >= 32 && (N & (N - 1)) == 0; }
 
-// Host FP32 [c][n3] -> BF16 [site][8] in s->x0, packed on the device.  The
-// FP32 values land in s->y (8 floats a site), which holds nothing before the
-// forward pass.
+// Up to this size the host puts input and output in order itself, which takes
+// about as long as the two launches, and waits for the upload by itself: the
+// runtime polls for a short while and then sleeps, 25 us more, so one long wait
+// may cost more than two short ones (forward of 16^3, two fields, 4, 5 and 6
+// layers 85, 96 and 108 us, ordered on the device 103, 115 and 126; 2 and 8
+// layers 62 and 160 against 55 and 150).
+constexpr int kHostOrderN = 16;
+
+// Host FP32 [c][n3] -> BF16 [site][8] in s->x0, packed on the device but for the
+// smallest lattices.  The FP32 values land in s->y (8 floats a site), which holds
+// nothing before the forward pass.
 cl_status upload_input(cl_surrogate* s, int N, const float* x) {
     const size_t n3 = static_cast<size_t>(N) * N * N;
     const int c = cin0(s);
+    if (N <= kHostOrderN) {
+        try {
+            s->hx.assign(n3 * 8, 0);
+        } catch (const std::bad_alloc&) {
+            return sfail(CL_ENOMEM, "host staging buffer");
+        }
+        for (int k = 0; k < c; ++k)
+            for (size_t i = 0; i < n3; ++i) {
+                uint32_t u;
+                std::memcpy(&u, &x[k * n3 + i], 4);
+                u += 0x7FFFu + ((u >> 16) & 1u);
+                s->hx[i * 8 + k] = static_cast<uint16_t>(u >> 16);
+            }
+        SHIP(hipMemcpyAsync(s->x0, s->hx.data(), n3 * 8 * sizeof(uint16_t), hipMemcpyHostToDevice, s->stream));
+        SHIP(hipStreamSynchronize(s->stream));
+        return CL_OK;
+    }
     SHIP(hipMemcpyAsync(s->y, x, c * n3 * sizeof(float), hipMemcpyHostToDevice, s->stream));
     SHIP(cl::sg::launch_pack_input(s->y, c, n3, s->x0, s->stream));
     return CL_OK;
@@ -647,6 +674,18 @@ cl_status cl_surrogate_forward(cl_surrogate* s, int N, const float* x, float* y)
     if (st) return st;
     const size_t n3 = static_cast<size_t>(N) * N * N;
     const int ys = ystride(s), co = s->L.back().cout;
+    if (N <= kHostOrderN) {
+        try {
+            s->hy.resize(n3 * ys);
+        } catch (const std::bad_alloc&) {
+            return sfail(CL_ENOMEM, "host staging buffer");
+        }
+        SHIP(hipMemcpyAsync(s->hy.data(), s->y, n3 * ys * sizeof(float), hipMemcpyDeviceToHost, s->stream));
+        SHIP(hipStreamSynchronize(s->stream));
+        for (int c = 0; c < co; ++c)
+            for (size_t i = 0; i < n3; ++i) y[c * n3 + i] = s->hy[i * ys + c];
+        return CL_OK;
+    }
     // the input (16 bytes a site) has been used: room for the at most 4 output channels
     float* out = reinterpret_cast<float*>(s->x0);
     SHIP(cl::sg::launch_channels_first(s->y, ys, co, n3, out, s->stream));

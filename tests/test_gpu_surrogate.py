@@ -90,6 +90,19 @@ def test_forward_of_repeated_input(n, N):
     s.close()
 
 
+@pytest.mark.parametrize("nf,extra", [(1, 0), (1, 3), (2, 1), (2, 4)])
+def test_forward_of_smallest_lattice(nf, extra):
+    """At 16^3 the host puts input and output in order, from 32^3 on the device:
+    the output of a 16^3 input repeated to 32^3 is that of 16^3 repeated, value
+    for value, also for values that BF16 does not hold and after another input."""
+    lib = _lib()
+    s = lib.Surrogate(n_fields=nf, extra_inputs=extra, layers=3, init_seed=8)
+    for seed, scale in ((1, 1.0), (2, 1e-40)):
+        x = (scale * np.random.default_rng(seed).standard_normal((s.cin, 16, 16, 16))).astype(np.float32)
+        assert np.array_equal(s.forward(np.tile(x, (1, 2, 2, 2))), np.tile(s.forward(x), (1, 2, 2, 2)))
+    s.close()
+
+
 def emulated_backward(params, x, t):
     """FP64 forward and backward with the GPU's BF16 roundings (the layer
     inputs and weights, the output gradient 2 (y - t) / n, the
