@@ -17,12 +17,11 @@ struct ConvArgs {
     float* z_out;        // FP32 [site][z_stride] (pre-activation) or null
     void* zh_out;        // BF16 [site][zh_stride] pre-activation (kept for the backward pass) or null
     int zh_stride;
-    void* a_out;         // BF16 [site][a_stride] (GELU(z) if gelu, else z) or null
+    void* a_out;         // BF16 [site][a_stride] (GELU(z)) or null
     const void* gz;      // BF16 [site][gz_stride] or null: a_out = z * GELU'(gz) (input gradient
                          // through the activation of the layer below)
     int gz_stride;
-    int N;
-    int nsites;          // N^3, a multiple of 16
+    int N;               // a multiple of 16
     int cout;            // output channels stored (multiple of 4)
     int z_stride, a_stride;
     int gelu;
@@ -96,7 +95,7 @@ struct UnpackArgs {
     int ystride;
 };
 
-hipError_t launch_conv_fwd(const ConvArgs& a, int cin, int nb, int grid, hipStream_t s);
+hipError_t launch_conv_fwd(const ConvArgs& a, int cin, int nb, hipStream_t s);
 hipError_t launch_conv_wgrad(const WgradArgs& a, int cin, hipStream_t s);
 hipError_t launch_wgrad_reduce(const WgradReduceArgs& a, hipStream_t s);
 hipError_t launch_mse_grad(const float* y, int ystride, const float* t, int cout, size_t nsites, double scale,

@@ -51,11 +51,7 @@ __device__ __forceinline__ uint32_t cvt2(float lo, float hi) {
 }
 __device__ __forceinline__ uint2 cvt4(const float* f) { return make_uint2(cvt2(f[0], f[1]), cvt2(f[2], f[3])); }
 
-// 4 BF16 values packed in two words <-> FP32
-__device__ __forceinline__ uint2 pack4(const uint16_t* h) {
-    return make_uint2(static_cast<uint32_t>(h[0]) | (static_cast<uint32_t>(h[1]) << 16),
-                      static_cast<uint32_t>(h[2]) | (static_cast<uint32_t>(h[3]) << 16));
-}
+// Two words of 4 packed BF16 values to FP32
 __device__ __forceinline__ void unpack4(uint2 u, float* f) {
     f[0] = __builtin_bit_cast(float, u.x << 16);
     f[1] = __builtin_bit_cast(float, u.x & 0xFFFF0000u);
@@ -77,20 +73,15 @@ __device__ __forceinline__ bf16x8 zero8() { return __builtin_bit_cast(bf16x8, ma
 // erfcc; relative error below 1.2e-7 for all x >= 0, so also in the negative
 // tail where Phi is small), with the hardware reciprocal and exp2: one rcp, two
 // exp2 and ten FMAs instead of the library's branchy erff and expf.
+constexpr float kErfc[10] = {0.17087277f,  -0.82215223f, 1.48851587f, -1.13520398f, 0.27886807f,
+                             -0.18628806f, 0.09678418f,  0.37409196f, 1.00002368f,  -1.26551223f};
+constexpr float kLog2e = 1.4426950408889634f;
 __device__ __forceinline__ float phi_cdf(float z, float* dens) {
     const float x = fabsf(z) * 0.70710678118654752f;
     const float t = __builtin_amdgcn_rcpf(fmaf(0.5f, x, 1.0f));
-    float p = 0.17087277f;
-    p = fmaf(p, t, -0.82215223f);
-    p = fmaf(p, t, 1.48851587f);
-    p = fmaf(p, t, -1.13520398f);
-    p = fmaf(p, t, 0.27886807f);
-    p = fmaf(p, t, -0.18628806f);
-    p = fmaf(p, t, 0.09678418f);
-    p = fmaf(p, t, 0.37409196f);
-    p = fmaf(p, t, 1.00002368f);
-    p = fmaf(p, t, -1.26551223f);
-    constexpr float kLog2e = 1.4426950408889634f;
+    float p = kErfc[0];
+#pragma unroll
+    for (int i = 1; i < 10; ++i) p = fmaf(p, t, kErfc[i]);
     const float mx2 = -x * x;
     const float half_erfc = 0.5f * t * __builtin_amdgcn_exp2f((mx2 + p) * kLog2e);
     if (dens) *dens = 0.39894228040143268f * __builtin_amdgcn_exp2f(mx2 * kLog2e);
@@ -105,111 +96,7 @@ __device__ __forceinline__ float gelu_grad(float z) {
     return c + z * d;
 }
 
-// Periodic neighbour of site (x, y, z) at stencil offset o.
-__device__ __forceinline__ int neighbour(int x, int y, int z, int o, int N) {
-    const int dx = o / 9 - 1, dy = (o / 3) % 3 - 1, dz = o % 3 - 1;
-    int xx = x + dx, yy = y + dy, zz = z + dz;
-    xx = xx < 0 ? xx + N : (xx >= N ? xx - N : xx);
-    yy = yy < 0 ? yy + N : (yy >= N ? yy - N : yy);
-    zz = zz < 0 ? zz + N : (zz >= N ? zz - N : zz);
-    return (xx * N + yy) * N + zz;
-}
-
 // ---------------------------------------------------------------- forward
-// One wave computes 16-site groups (consecutive z in one row) x NB*16
-// output channels, GPW groups at a time sharing each weight fragment.
-template <int CIN, int NB, int GPW>
-__global__ __launch_bounds__(256) void conv_fwd(ConvArgs a) {
-    constexpr int NO = CIN == 32 ? 27 : 28;       // stencil offsets stored (padded for CIN == 8)
-    constexpr int KSTEPS = CIN == 32 ? 27 : 7;    // MFMAs along K per output block
-    constexpr int WSZ = NO * NB * 16 * CIN;       // bf16 elements of the weights
-    extern __shared__ __align__(16) uint16_t wlds[];
-    const uint16_t* __restrict__ wg = reinterpret_cast<const uint16_t*>(a.w);
-    for (int i = threadIdx.x * 8; i < WSZ; i += blockDim.x * 8)
-        *reinterpret_cast<uint4*>(wlds + i) = *reinterpret_cast<const uint4*>(wg + i);
-    __syncthreads();
-
-    const uint16_t* __restrict__ in = reinterpret_cast<const uint16_t*>(a.in);
-    const int N = a.N;
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    const int n = lane & 15;     // site within the group / B column
-    const int g = lane >> 4;     // k-group
-    const int ngroups = a.nsites / 16;
-    const int wave_id = blockIdx.x * 4 + wave;
-    const int nwaves = gridDim.x * 4;
-    for (int gb = wave_id * GPW; gb < ngroups; gb += nwaves * GPW) {
-        int sx[GPW], sy[GPW], sz[GPW];
-        bool valid[GPW];
-#pragma unroll
-        for (int q = 0; q < GPW; ++q) {
-            const int grp = gb + q;
-            valid[q] = grp < ngroups;
-            const int site = (valid[q] ? grp : 0) * 16 + n;
-            sz[q] = site % N;
-            sy[q] = (site / N) % N;
-            sx[q] = site / (N * N);
-        }
-        f32x4 acc[GPW][NB];
-#pragma unroll
-        for (int q = 0; q < GPW; ++q)
-#pragma unroll
-            for (int b = 0; b < NB; ++b) acc[q][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 3
-        for (int s = 0; s < KSTEPS; ++s) {
-            // weight fragments (A) of this K step for every output block
-            const int o = CIN == 32 ? s : 4 * s + g;  // stencil offset this lane's k-group reads
-            const int cbase = CIN == 32 ? 8 * g : 0;  // first input channel of the k-group
-            bf16x8 wa[NB];
-#pragma unroll
-            for (int b = 0; b < NB; ++b) wa[b] = load8(wlds + ((o * NB * 16) + b * 16 + n) * CIN + cbase);
-#pragma unroll
-            for (int q = 0; q < GPW; ++q) {
-                bf16x8 xb = zero8();
-                if (valid[q] && o < 27) xb = load8(in + static_cast<size_t>(neighbour(sx[q], sy[q], sz[q], o, N)) * CIN + cbase);
-#pragma unroll
-                for (int b = 0; b < NB; ++b)
-                    acc[q][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa[b], xb, acc[q][b], 0, 0, 0);
-            }
-        }
-        // epilogue: lane holds output channels 16b + 4g + r of site (group, n)
-#pragma unroll
-        for (int q = 0; q < GPW; ++q) {
-            if (!valid[q]) continue;
-            const size_t site = static_cast<size_t>(gb + q) * 16 + n;
-#pragma unroll
-            for (int b = 0; b < NB; ++b) {
-                const int c0 = 16 * b + 4 * g;
-                if (c0 >= a.cout) continue;
-                float v[4];
-#pragma unroll
-                for (int r = 0; r < 4; ++r) v[r] = acc[q][b][r] + (a.bias ? a.bias[c0 + r] : 0.f);
-                if (a.z_out) *reinterpret_cast<float4*>(a.z_out + site * a.z_stride + c0) = make_float4(v[0], v[1], v[2], v[3]);
-                if (a.zh_out) {
-                    const uint16_t zh[4] = {f2bf(v[0]), f2bf(v[1]), f2bf(v[2]), f2bf(v[3])};
-                    *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.zh_out) + site * a.zh_stride + c0) = pack4(zh);
-                }
-                if (a.a_out) {
-                    uint16_t h[4];
-                    if (a.gz) {
-                        float zv[4];
-                        unpack4(*reinterpret_cast<const uint2*>(reinterpret_cast<const uint16_t*>(a.gz) + site * a.gz_stride + c0), zv);
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) h[r] = f2bf(v[r] * gelu_grad(zv[r]));
-                    } else {
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) h[r] = f2bf(a.gelu ? gelu(v[r]) : v[r]);
-                    }
-                    uint2 pk;
-                    pk.x = static_cast<uint32_t>(h[0]) | (static_cast<uint32_t>(h[1]) << 16);
-                    pk.y = static_cast<uint32_t>(h[2]) | (static_cast<uint32_t>(h[3]) << 16);
-                    *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.a_out) + site * a.a_stride + c0) = pk;
-                }
-            }
-        }
-    }
-}
-
 // What the tiled convolutions make of their FP32 sums plus bias v: z_out = v
 // (kEpiZ), a_out = GELU(v) (kEpiGelu), that and zh_out = v (kEpiGeluKeep, when
 // the backward pass follows), or a_out = v GELU'(gz) (kEpiGeluGrad).
@@ -235,9 +122,6 @@ constexpr int kEpiStages = 11;
 
 template <int MODE, int S>
 __device__ __forceinline__ void epi_stage(EpiState& e, const f32x4 v, uint2 gz, uint2& out) {
-    constexpr float kLog2e = 1.4426950408889634f;
-    constexpr float kP[10] = {0.17087277f, -0.82215223f, 1.48851587f, -1.13520398f, 0.27886807f,
-                              -0.18628806f, 0.09678418f, 0.37409196f, 1.00002368f, -1.26551223f};
     float z[4] = {v[0], v[1], v[2], v[3]};
     if constexpr (MODE == kEpiGeluGrad) unpack4(gz, z);
     if constexpr (MODE == kEpiZ) return;
@@ -248,12 +132,12 @@ __device__ __forceinline__ void epi_stage(EpiState& e, const f32x4 v, uint2 gz, 
             e.t[q] = fmaf(0.5f, e.x[q], 1.0f);
         } else if constexpr (S == 1) {
             e.t[q] = __builtin_amdgcn_rcpf(e.t[q]);
-            e.p[q] = kP[0];
+            e.p[q] = kErfc[0];
         } else if constexpr (S <= 5) {
-            e.p[q] = fmaf(e.p[q], e.t[q], kP[2 * S - 3]);
-            e.p[q] = fmaf(e.p[q], e.t[q], kP[2 * S - 2]);
+            e.p[q] = fmaf(e.p[q], e.t[q], kErfc[2 * S - 3]);
+            e.p[q] = fmaf(e.p[q], e.t[q], kErfc[2 * S - 2]);
         } else if constexpr (S == 6) {
-            e.p[q] = fmaf(e.p[q], e.t[q], kP[9]);
+            e.p[q] = fmaf(e.p[q], e.t[q], kErfc[9]);
             e.x[q] = -e.x[q] * e.x[q];
             if constexpr (MODE == kEpiGeluGrad) e.d[q] = e.x[q] * kLog2e;
         } else if constexpr (S == 7) {
@@ -501,6 +385,7 @@ __global__ __launch_bounds__(512, 2) void conv32_march(ConvArgs a, int L) {
 // with GELU; four waves a tile with both blocks and all rows at once: 103 us).
 template <int RY, int MODE>
 __global__ __launch_bounds__(512, 4) void conv8_fwd_tiled(ConvArgs a) {
+    static_assert(MODE != kEpiZ, "no layer of 8 inputs ends in plain sums");
     constexpr int ZR = 18, YR = RY + 2, PL = 6, KS = 7;
     __shared__ __align__(16) uint16_t tin[PL * YR * ZR * 8];
     const uint16_t* __restrict__ in = reinterpret_cast<const uint16_t*>(a.in);
@@ -573,13 +458,9 @@ __global__ __launch_bounds__(512, 4) void conv8_fwd_tiled(ConvArgs a) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) u[q] = acc[q] + bias[q];
         const size_t site = site0 + r * N;
-        if constexpr (MODE == kEpiZ) {
-            *reinterpret_cast<f32x4*>(a.z_out + site * a.z_stride + c0) = f32x4{u[0], u[1], u[2], u[3]};
-        } else {
-            if constexpr (MODE == kEpiGeluKeep)
-                *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.zh_out) + site * a.zh_stride + c0) = cvt4(u);
-            *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.a_out) + site * a.a_stride + c0) = epilogue4<MODE>(u, zg[r]);
-        }
+        if constexpr (MODE == kEpiGeluKeep)
+            *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.zh_out) + site * a.zh_stride + c0) = cvt4(u);
+        *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.a_out) + site * a.a_stride + c0) = epilogue4<MODE>(u, zg[r]);
     }
 }
 
@@ -993,17 +874,15 @@ __global__ void unpack_jump(UnpackArgs a) {
 }
 
 // Host-side launchers ------------------------------------------------------
-hipError_t launch_conv_fwd(const ConvArgs& a, int cin, int nb, int grid, hipStream_t s) {
-    const int no = cin == 32 ? 27 : 28;
-    const size_t lds = static_cast<size_t>(no) * nb * 16 * cin * 2;
-    // the outputs of one of the tiled kernels' epilogues, or of none of them
+hipError_t launch_conv_fwd(const ConvArgs& a, int cin, int nb, hipStream_t s) {
+    // the outputs of one of the epilogues, or of none of them
     const bool z = a.z_out && !a.zh_out && !a.a_out, act = !a.z_out && a.a_out;
     const int mode = z                                  ? kEpiZ
                      : act && a.gz && !a.zh_out         ? kEpiGeluGrad
                      : act && !a.gz && a.gelu           ? (a.zh_out ? kEpiGeluKeep : kEpiGelu)
                                                         : -1;
-    const bool tiled = a.N >= 16 && a.N % 16 == 0 && mode >= 0 && (a.cout == 32 || mode == kEpiZ);
-    if (cin == 32 && tiled && (nb == 2 ? a.cout == 32 : mode == kEpiZ && a.cout <= 16)) {
+    if (mode < 0 || a.N < 16 || a.N % 16) return hipErrorInvalidValue;
+    if (cin == 32 && (nb == 2 ? a.cout == 32 : nb == 1 && mode == kEpiZ && a.cout <= 16)) {
         // one column of 8 x 16 output sites per workgroup, its march in as many
         // pieces as fill the chip once: a workgroup has a CU to itself (115 KB of
         // LDS), and every piece pays for its weights, its first six planes and the
@@ -1018,18 +897,15 @@ hipError_t launch_conv_fwd(const ConvArgs& a, int cin, int nb, int grid, hipStre
                  : mode == kEpiGeluKeep  ? conv32_march<8, 2, kEpiGeluKeep>
                                          : conv32_march<8, 2, kEpiGeluGrad>;
         hipLaunchKernelGGL(k, dim3(cols * ((steps + L - 1) / L)), dim3(512), 0, s, a, L);
-    } else if (cin == 8 && nb == 2 && tiled && a.cout == 32) {
+    } else if (cin == 8 && nb == 2 && a.cout == 32 && mode != kEpiZ) {
         // one workgroup per 4 x 8 x 16 block of output sites
-        auto k = mode == kEpiZ          ? conv8_fwd_tiled<8, kEpiZ>
-                 : mode == kEpiGelu     ? conv8_fwd_tiled<8, kEpiGelu>
+        auto k = mode == kEpiGelu       ? conv8_fwd_tiled<8, kEpiGelu>
                  : mode == kEpiGeluKeep ? conv8_fwd_tiled<8, kEpiGeluKeep>
                                         : conv8_fwd_tiled<8, kEpiGeluGrad>;
         hipLaunchKernelGGL(k, dim3((a.N / 4) * (a.N / 8) * (a.N / 16)), dim3(512), 0, s, a);
-    } else if (cin == 32 && nb == 2) hipLaunchKernelGGL((conv_fwd<32, 2, 4>), dim3(grid), dim3(256), lds, s, a);
-    else if (cin == 32 && nb == 1) hipLaunchKernelGGL((conv_fwd<32, 1, 4>), dim3(grid), dim3(256), lds, s, a);
-    else if (cin == 8 && nb == 2) hipLaunchKernelGGL((conv_fwd<8, 2, 4>), dim3(grid), dim3(256), lds, s, a);
-    else if (cin == 8 && nb == 1) hipLaunchKernelGGL((conv_fwd<8, 1, 4>), dim3(grid), dim3(256), lds, s, a);
-    else return hipErrorInvalidValue;
+    } else {
+        return hipErrorInvalidValue;
+    }
     return hipGetLastError();
 }
 

@@ -209,7 +209,6 @@ cl_status prepare(cl_surrogate* s) {
 // Network forward from s->x0; training keeps the pre-activations.
 cl_status forward(cl_surrogate* s, int N, bool training) {
     const int nl = static_cast<int>(s->L.size());
-    const int n3 = N * N * N;
     for (int l = 0; l < nl; ++l) {
         const Layer& ly = s->L[l];
         ConvArgs a{};
@@ -217,7 +216,6 @@ cl_status forward(cl_surrogate* s, int N, bool training) {
         a.w = ly.wf;
         a.bias = ly.bias;
         a.N = N;
-        a.nsites = n3;
         a.cout = ly.coutp == 16 ? 4 * ((ly.cout + 3) / 4) : 32;
         if (l + 1 < nl) {
             a.z_out = nullptr;
@@ -232,9 +230,7 @@ cl_status forward(cl_surrogate* s, int N, bool training) {
             a.a_out = nullptr;
             a.gelu = 0;
         }
-        const int groups = n3 / 16;
-        const int grid = std::max(1, std::min(1024, (groups + 15) / 16));
-        SHIP(cl::sg::launch_conv_fwd(a, ly.cinp, ly.nb, grid, s->stream));
+        SHIP(cl::sg::launch_conv_fwd(a, ly.cinp, ly.nb, s->stream));
     }
     return CL_OK;
 }
@@ -285,7 +281,6 @@ cl_status loss_and_backward(cl_surrogate* s, int N, double* loss, bool input_gra
             a.w = ly.wd;
             a.bias = nullptr;
             a.N = N;
-            a.nsites = static_cast<int>(n3);
             a.cout = 32;
             a.gelu = 0;
             uint16_t* next = s->dZ[(nl - 1 - l) & 1];
@@ -300,9 +295,7 @@ cl_status loss_and_backward(cl_surrogate* s, int N, double* loss, bool input_gra
                 a.z_stride = 32;
                 a.a_out = nullptr;
             }
-            const int groups = static_cast<int>(n3 / 16);
-            const int grid2 = std::max(1, std::min(1024, (groups + 15) / 16));
-            SHIP(cl::sg::launch_conv_fwd(a, ly.cinp_d, 2, grid2, s->stream));
+            SHIP(cl::sg::launch_conv_fwd(a, ly.cinp_d, 2, s->stream));
             dz = next;
             dz_stride = 32;
         }
