@@ -2026,7 +2026,7 @@ cl_status cl_ensemble_get_tile(const cl_ensemble* e, int i, cl_tile* out) {
     out->ty = t.TY;
     out->cx = t.CX;
     out->ry = t.RY;
-    out->pd = t.RY == 1 ? 4 : 2;  // the prefetch depth does not change the results
+    out->pd = e->maxry == 1 ? 4 : 2;  // the kernel's, for every member (it does not change the results)
     return CL_OK;
 }
 

@@ -170,3 +170,19 @@ def test_config2_ensemble_sampled_members():
         solo.close()
         assert rs.tobytes() == np.ascontiguousarray(r[:, i]).tobytes(), i
         assert np.array_equal(f, fields[i]), i
+
+
+@pytest.mark.parametrize("sizes", [(32,), (64,), (32, 64)])
+def test_reported_depth_is_the_kernels(sizes):
+    """The kernel of an ensemble with two-row members runs every member at depth
+    2, that of one-row members alone at depth 4."""
+    lib = __import__("paper_2607_24978_amd._lib", fromlist=["_lib"])
+    lats = [lib.Lattice(N, 0.5, 1, "fp32") for N in sizes]
+    ens = lib.Ensemble(lats)
+    tiles = [ens.get_tile(i) for i in range(len(sizes))]
+    two_rows = any(t["ry"] == 2 for t in tiles)
+    assert two_rows == (64 in sizes) and tiles[0]["ry"] == (1 if sizes[0] == 32 else 2)
+    assert all(t["pd"] == (2 if two_rows else 4) for t in tiles)
+    ens.close()
+    for lat in lats:
+        lat.close()
