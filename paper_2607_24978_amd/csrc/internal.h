@@ -74,11 +74,12 @@ struct Tile {
 // (kPassReverse).  Whether the written state stays cached (ordinary stores)
 // or streams past (kPassNtStore) depends on the bytes a pass touches: up to
 // twice the cache the reuse wins, beyond it the streaming stores do.
-// Measured on MI355X, us per pass, ordinary / streaming: one field 256^3 FP32
-// (256 MiB touched) 41.5 / 59, two fields 128^3 FP64 (256 MiB) 29.8 / 39.7,
-// two fields 256^3 FP32 (512 MiB) 99.7 / 103.5 (106 ordinary without the
-// reversed passes), one field 384^3 FP64 (864 MiB) 359 / 346, two fields
-// 512^3 FP32 (2 GiB) 741 / 722.
+// Measured on MI355X, us per pass, ordinary / streaming: two fields 128^3 FP64
+// (128 MiB touched) 29.8 / 39.7, one field 256^3 FP32 (256 MiB) 41.5 / 59, two
+// fields 256^3 FP32 (512 MiB) 99.7 / 103.5 (106 ordinary without the reversed
+// passes), one field 384^3 FP64 (1.7 GiB) 359 / 346, two fields 512^3 FP32
+// (4 GiB) 741 / 722.  Runge-Kutta, four rk4 steps, with the register counted:
+// one field 256^3 FP32 (384 MiB) 1993 / 2047, two fields (768 MiB) 3666 / 3566.
 constexpr int kPassNtStore = 1;
 constexpr int kPassReverse = 2;
 constexpr size_t kMallBytes = size_t(256) << 20;
@@ -285,8 +286,8 @@ hipError_t launch_prop_ifftz_unpack(const PropZArgs& a, bool fp32, hipStream_t s
 // modes (out of place: its `in` then holds the z and y transforms, its `out`
 // what the inverse y pass takes).
 bool prop_modes_with_x(int N, bool fp32);
-// Transfer matrices (FP64) and their application to every mode; fp32: the
-// arrays hold float2 values (converted to FP64 for the product).
+// Transfer matrices (formed in FP64) and their application to every mode in the
+// arrays' precision (fp32: float2 values and FP32 matrices).
 hipError_t launch_prop_modes(const PropModeArgs& a, bool fp32, hipStream_t s);
 hipError_t launch_init_scalars(Scal* sc, double a, double b, double eta, const Phys& ph,
                                const double* shift, hipStream_t s);

@@ -1802,7 +1802,7 @@ cl_status ens_upload_table(cl_ensemble* e, bool with_dt) {
 // the lattice is tall enough: about 32k sites, or fewer until at least every
 // second workgroup that can run at once has an item.  Measured (one field,
 // FP32, 512 workgroups at once), us per pass with 8k / 16k / 32k / 64k-site
-// items: 48 x 32^3 (192 .. 24 items) 22.7 / 27.1 / 40.4 / -, 32 x 64^3 (1024 ..
+// items: 48 x 32^3 (192 .. 48 items) 22.7 / 27.1 / 40.4 / -, 32 x 64^3 (1024 ..
 // 128) 44.0 / 37.9 / 37.3 / 54.8, 16 x 128^3 (4096 .. 512) 134 / 117 / 108 / 109.
 int ens_item_sites(const cl_ensemble* e) {
     int sites = 32768;

@@ -24,8 +24,8 @@
 // x, y, z), so the state is read once and written once per jump.  The
 // transforms run in the state's precision: FP32 lattices use float2 values,
 // whose rounding (relative to the fluctuations, from which the means are
-// removed) is far below that of the FP32 state itself; the transfer matrices
-// and their product with a mode are FP64 for both.
+// removed) is far below that of the FP32 state itself.  The transfer matrices
+// are formed in FP64 and rounded once to that precision, in which they act.
 #include "fft_lds.h"
 #include "fft_reg.h"
 #include "internal.h"

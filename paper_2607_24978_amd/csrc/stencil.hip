@@ -15,11 +15,12 @@
 // since the drift of halo cells needs the old momenta of neighbouring tiles.
 //
 // Blocking: a workgroup owns a TZ x TY tile of (z, y) and marches over CX
-// x-planes, up or (kPassReverse) down.  Each x-plane of drifted f (tile plus a one-cell y/z halo) is
-// staged in LDS (double-buffered, one barrier per plane); the x-neighbours
+// x-planes, up or (kPassReverse) down.  Each x-plane of drifted f (tile plus a
+// one-cell y/z halo) is staged in LDS (double-buffered, one barrier per plane); the x-neighbours
 // live in registers.  Each thread owns V consecutive z values (16-byte
 // vector loads and stores) in RY rows.
 #include "internal.h"
+#include "static_for.h"
 #include "xcd_order.h"
 
 #include <hip/hip_runtime.h>
@@ -374,15 +375,6 @@ struct TileJob {
     int rk_first, rk_last;
 };
 
-// Calls f(integral_constant<int, B>), ..., f(integral_constant<int, E - 1>).
-template <int B, int E, typename F>
-__device__ __forceinline__ void static_for(F&& f) {
-    if constexpr (B < E) {
-        f(std::integral_constant<int, B>{});
-        static_for<B + 1, E>(f);
-    }
-}
-
 // RK = 0: fused drift + kick (the symplectic schemes).  RK = 1: one
 // low-storage Runge-Kutta stage -- no drift (the plane staged in LDS is the
 // stage's input f), F = h (a^(alpha-3) pi, a^(1+alpha) L f - a^(3+alpha) dV),
@@ -607,7 +599,7 @@ __device__ __forceinline__ void march_tile(const TileJob& J, unsigned char* smem
     issue(S0{}, S0{}, -1, kNone);
     if constexpr (PD >= 2) {
         issue(S1{}, hs(K0{}), 0, 0);
-        static_for<2, PD>([&](auto Sc) {
+        static_for<PD, 2>([&](auto Sc) {
             constexpr int s_ = decltype(Sc)::value;
             using Km = std::integral_constant<int, s_ - 1>;
             if (s_ - 1 <= CX) issue(Sc, hs(Km{}), s_ - 1, HPD == PD ? s_ - 1 : kNone);
@@ -852,7 +844,7 @@ __device__ __forceinline__ void march_tile(const TileJob& J, unsigned char* smem
                 }
     };
     for (int i = 0; i < CX; i += PD) {
-        static_for<0, PD>([&](auto Sc) {
+        static_for<PD>([&](auto Sc) {
             constexpr int s_ = decltype(Sc)::value;
             // body(i) takes plane i + 1: set (i + 2) mod PD and halo set
             // hs(i + 1) (i is a multiple of PD here), the one set (PD = 1)
@@ -1106,7 +1098,7 @@ static int march_length(int N, int tiles, int per_round) {
 // long number at most two per CU, two waves up to 64^3, four while the state
 // reuses the memory-side cache, and eight beyond it, where the halo rows of
 // short tiles are read from HBM again.  (At exactly twice the cache one field
-// takes eight and two fields four: two leapfrog steps of 256^3 FP64 one field
+// takes eight and two fields four: four leapfrog steps of 256^3 FP64 one field
 // 529 us against 559 with four, of 256^3 FP32 two fields 569 against 531.)
 // Measured, us per pass against the former tile (256 threads, marches of at
 // least four planes): one field 32^3 FP64 8.9 / 11.1, two fields 64^3 FP32
@@ -1114,9 +1106,9 @@ static int march_length(int N, int tiles, int per_round) {
 // 108.9, one field 384^3 FP64 344 / 382, two fields 512^3 FP32 721 / 798 (with
 // the cache policy above).
 // Marches are counted in rounds of one workgroup per CU, or of two where their
-// registers allow it and there is work for them, four waves of one field:
-// 256^3 FP32 54 us a pass against 58 with marches of twice the length, its
-// Runge-Kutta stages 84 against 93 (rk4), 128^3 FP32 19.1 / 19.5.
+// registers allow it and there is work for them, four waves of one field: ten
+// leapfrog steps of 256^3 FP32 548 us against 585 with marches of twice the
+// length, ten rk4 steps 4.23 ms against 4.65, leapfrog of 128^3 FP32 191 / 195.
 Tile default_tile(int N, cl_precision prec, int nf) {
     const int V = prec == CL_FP32 ? 4 : 2;
     const size_t sites = static_cast<size_t>(N) * N * N;
@@ -1145,7 +1137,7 @@ Tile default_tile(int N, cl_precision prec, int nf) {
 // workgroups of half the march, 256^3 one field 958 / 1020).  Otherwise the
 // marches are halved up to 1024 workgroups, whose uneven ends overlap: 384^3
 // FP64, two steps, 7.9 ms with 1152 workgroups against 9.6 with 576, 512^3 FP32
-// one reduction after another 2.71 ms with 1024 against 2.84 with 512.
+// 7.27 ms with 1024 against 7.33 with 512.
 Tile gw_tile(int N, cl_precision prec) {
     constexpr int kAtOnce = 512;
     const int V = prec == CL_FP32 ? 4 : 2;
@@ -1198,9 +1190,11 @@ Tile reduction_tile(const Tile& t, int N, cl_precision prec, int nf) {
 // field) or one wave per SIMD.  With two rows one field is held to two waves
 // per SIMD, which takes a prefetch depth of 2: a plane step is bound by its
 // barrier and LDS round trips, so a second workgroup per CU is worth more
-// than deeper prefetch (two fields would spill, and keep one wave).  48 x 32^3 + 32 x 64^3 + 16 x 128^3, one
-// field, FP32 (696 MB per pass): 157 us = 4.4 TB/s against 200 at depth 4 and
-// one wave per SIMD (164 with one row and three waves).
+// than deeper prefetch.  48 x 32^3 + 32 x 64^3 + 16 x 128^3, one field, FP32
+// (696 MB per pass): 157 us = 4.4 TB/s against 200 at depth 4 and one wave per
+// SIMD (164 with one row and three waves).  Two fields would spill at two
+// waves and keep one; depth 2 leaves them without spills (the ensemble's ten
+// leapfrog steps 4.8 ms against 6.2 at depth 4, FP32).
 // Scalar blocks of an ensemble member inside a call: pass p starts from the
 // scalars pass p - 1 used (the member's own block for p = 1 and p = 0) and
 // leaves its own in scratch block p mod 2.
