@@ -1700,34 +1700,37 @@ cl_status ens_layout(cl_ensemble* e, int item_sites, bool two_rows) {
     const int n = static_cast<int>(e->m.size());
     std::vector<cl::EnsMember> table(n);
     std::vector<size_t> offs(n);
-    std::vector<cl::EnsItem> items;
+    std::vector<cl::EnsItem> items;  // of even passes, then of odd ones
+    std::vector<int> order(n);
     size_t poff = 0;
-    int maxTY = 0, maxTZ = 0;
+    int maxTY = 0, maxTZ = 0, nitems = 0;
     for (int i = 0; i < n; ++i) {
         cl::EnsMember t{};
         const int N = e->m[i]->N;
         if (!ensemble_tile(N, e->prec, t, item_sites, two_rows))
             return efail(CL_EUNSUPPORTED, "member " + std::to_string(i) + ": N = " + std::to_string(N) +
                                               " is too small for an ensemble tile (N >= 32 needed)");
-        for (int k = 0; k < t.nitems; ++k) items.push_back({i, k});
         offs[i] = poff;
         poff += 2 * static_cast<size_t>(cl::nsums(e->nf)) * t.nitems;  // two halves
         maxTY = std::max(maxTY, t.TY);
         maxTZ = std::max(maxTZ, t.TZ);
+        nitems += t.nitems;
         table[i] = t;
+        order[i] = i;
     }
-    // The order in which the workgroups take them: longest marches first, so that
+    // The order in which the workgroups take the items: longest marches first, so that
     // none starts when the others run out (48 x 32^3 + 32 x 64^3 + 16 x 128^3,
     // one field, FP32, us a pass: 157 in this order, 175 with the 32-plane items
     // of the 32^3 last).  While the stores stay in the memory-side cache, odd
     // passes go the other way among the items of one length and find the rows
     // written last there (16 x 128^3: 1327 us a ten-step call, 1401 without).
-    auto planes = [&](const cl::EnsItem& i) { return table[i.member].CX; };
-    std::stable_sort(items.begin(), items.end(),
-                     [&](const cl::EnsItem& a, const cl::EnsItem& b) { return planes(a) > planes(b); });
-    const int nitems = static_cast<int>(items.size());
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return table[a].CX > table[b].CX; });
+    items.reserve(2 * nitems);
+    for (int i : order)
+        for (int k = 0; k < table[i].nitems; ++k) items.push_back({i, k});
     items.resize(2 * nitems);
     std::copy(items.begin(), items.begin() + nitems, items.begin() + nitems);
+    auto planes = [&](const cl::EnsItem& i) { return table[i.member].CX; };
     if (!(cl::pass_flags(ens_bytes(e), 1) & cl::kPassNtStore))
         for (auto a = items.begin() + nitems; a != items.end();) {
             auto b = std::find_if(a, items.end(), [&](const cl::EnsItem& i) { return planes(i) != planes(*a); });
