@@ -810,7 +810,7 @@ __global__ void pack_state(PackArgs a) {
 }
 
 // Network input, FP32 [c][site], c <= 8, to BF16 [site][8].  One read and one
-// 16-byte write per site, 7.8 us for 64^3; the same loop on one host core takes
+// 16-byte write per site, 7 us for 64^3; the same loop on one host core takes
 // 630 us for 64^3.
 __global__ __launch_bounds__(256) void pack_input(const float* __restrict__ x, int c, size_t n3, uint16_t* __restrict__ out) {
     const size_t s = static_cast<size_t>(blockIdx.x) * blockDim.x + threadIdx.x;
